@@ -12,6 +12,15 @@
 #endif
 
 namespace snnlif {
+namespace {
+
+// The relay's workgroups: a wave per chunk, up to kRelayWaves.
+int relay_lanes(const Plan& p, int64_t T) {
+    const int64_t chunks = (T + p.k - 1) / p.k;
+    return kWave * int(chunks < kRelayWaves ? chunks : kRelayWaves);
+}
+
+}  // namespace
 
 #if !SNNLIF_GAIN
 
@@ -22,6 +31,13 @@ snn_status backward_entry(int reset, const Plan& p, const LifK& k, int64_t T, in
     const float* sv = static_cast<const float*>(saved);
     const BwdSeg seg{v_in, g_in, g_out};
     auto go = [&](auto rst) {
+        if (p.narrow) {
+            return narrow_variant(p, [&](auto K) {
+                constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
+                return launch_blk(lif_backward_relay_kernel<IO, R, Kc>, grid_for(N, kWave), relay_lanes(p, T), s, k, T,
+                                  N, x, sv, gs, gx, seg);
+            });
+        }
         return backward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
             constexpr int R = decltype(rst)::value;
             constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
@@ -60,6 +76,13 @@ snn_status backward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t 
     const uint8_t* si = static_cast<const uint8_t*>(spikes_in);
     const float* sv = static_cast<const float*>(saved);
     auto go = [&](auto rst) {
+        if (p.narrow) {
+            return narrow_variant(p, [&](auto K) {
+                constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
+                return launch_blk(lif_backward_gain_relay_kernel<IO, SPK, R, Kc>, grid_for(N, kWave), relay_lanes(p, T),
+                                  s, k, T, N, F, si, gain, p.row_bytes, sv, gs, gs_in);
+            });
+        }
         return backward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
             constexpr int R = decltype(rst)::value;
             constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;

@@ -23,6 +23,16 @@ snn_status forward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int
     uint8_t* sp = static_cast<uint8_t*>(spikes);
     float* sv = static_cast<float*>(saved);
     auto go = [&](auto rst) {
+        if (p.narrow) {
+            return narrow_variant(p, [&](auto K) {
+                constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
+                const dim3 g = grid_for(p.lanes * p.vf, kWave);
+                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, 1, Kc, Kc, true, true, kWave>, g, kWave, s, k,
+                                          T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last)
+                             : launch_blk(lif_forward_kernel<IO, SPK, R, 1, Kc, Kc, false, true, kWave>, g, kWave, s, k,
+                                          T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last);
+            });
+        }
         return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
             constexpr int R = decltype(rst)::value;
             constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
@@ -60,6 +70,16 @@ snn_status forward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t T
     float* sv = static_cast<float*>(saved);
     const dim3 g = grid_for(p.lanes);
     auto go = [&](auto rst) {
+        if (p.narrow) {
+            return narrow_variant(p, [&](auto K) {
+                constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
+                const dim3 gn = grid_for(p.lanes * p.vf, kWave);
+                return v_out ? launch_blk(lif_forward_gain_kernel<IO, SPK, R, 1, Kc, Kc, true, true, kWave>, gn, kWave,
+                                          s, k, T, N, F, si, gain, sp, p.row_bytes, sv, v_out)
+                             : launch_blk(lif_forward_gain_kernel<IO, SPK, R, 1, Kc, Kc, false, true, kWave>, gn, kWave,
+                                          s, k, T, N, F, si, gain, sp, p.row_bytes, sv, v_out);
+            });
+        }
         return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
             constexpr int R = decltype(rst)::value;
             constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;

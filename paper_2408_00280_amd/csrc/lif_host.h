@@ -51,6 +51,8 @@ struct Plan {
     int blkf;        // workgroup sizes of the dense forward and backward kernels
     int blkb;
     bool syncb;      // the backward's kSyncBlock workgroups meet at a barrier after each chunk
+    bool narrow;     // few neurons, several chunks: one neuron per lane in place of vf and vb,
+                     // the forward in one-wave workgroups, the backward as a relay of waves
     int64_t lanes;   // lanes in the forward grid
     int64_t row_bytes;
 };
@@ -87,6 +89,16 @@ constexpr int64_t kFillLanes = int64_t(256) * 16 * 64;
 constexpr int kSyncBlock = 1024;
 constexpr int kSyncBf16Chunks = 6;
 
+// A layer of several chunks with at most this many neurons (5 waves per CU at one neuron
+// per lane) runs one neuron per lane, in workgroups of one wave, double-buffered, and its
+// backward as a relay of waves (backward_relay): twice the lanes of the wider plan, and as
+// many CUs as there are waves.  Its chunk length stays that of the wider plan.  Measured
+// against 2 neurons per lane in 256-lane workgroups, fp32 forward: x[1000][8192] 52.5 ->
+// 28.9 us, [200][16384] 14.2 -> 8.2 us, [200][65536] 19.0 -> 14.7 us, [200][80000] 20.1 ->
+// 17.3 us, [200][98304] 21.6 -> 20.9 us (bf16 17.2 -> 19.6 us); backward [200][80000] 41.3
+// -> 37.0 us, [200][98304] 44.6 -> 46.6 us: hence the limit.
+constexpr int64_t kNarrowN = 5 * int64_t(256) * 64;
+
 inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     Plan p;
     // 2 neurons per lane (fp32 8-byte rows: 4 per lane measured 1% slower on large layers;
@@ -111,6 +123,7 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     p.blkf = long_walk && p.vf >= 2 ? kSyncBlock : kBlock;   // the lane widths measured
     p.blkb = long_walk && p.vb == 2 ? kSyncBlock : kBlock;
     p.syncb = c->io == SNN_IO_F32 || (T + p.k - 1) / p.k <= kSyncBf16Chunks;
+    p.narrow = T > p.k && N <= kNarrowN;
     p.row_bytes = spike_row_bytes(c, N);
     const int64_t covered = c->spk == SNN_SPK_BITS ? p.row_bytes * 8 : N;
     p.lanes = (covered + p.vf - 1) / p.vf;
@@ -119,7 +132,7 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
 
 // The layer fed by the previous layer's spikes reads one spike word per lane and row (2-8
 // bytes) where the dense layer reads an I/O row of 8-16 bytes, so double-buffering its
-// chunks costs more in occupancy than it hides (fp32 backward: 191 instead of 79 VGPRs, 2
+// chunks costs more in occupancy than it hides, but for the few lanes of a narrow layer (fp32 backward: 191 instead of 79 VGPRs, 2
 // instead of 6 waves per SIMD; forward 127 instead of 69).  Its chunks are single-buffered
 // at the dense layer's chunk length, so the checkpoint layout and snn_lif_saved_bytes stay
 // the dense layer's.  At N = 2^19 (event timing, three alternating rounds): fp32 u8 spikes,
@@ -223,6 +236,16 @@ constexpr int forward_batch(int io, int v, int k, bool pipe) {
 // combinations a kernel translation unit instantiates.
 template <int I>
 using IntC = std::integral_constant<int, I>;
+
+// The chunk lengths of a narrow layer: those of the plans of 2 neurons (even N) and of 1.
+template <typename F>
+snn_status narrow_variant(const Plan& p, F&& f) {
+    switch (p.k) {
+        case chunk_steps(2): return f(IntC<chunk_steps(2)>{});
+        case chunk_steps(1): return f(IntC<chunk_steps(1)>{});
+    }
+    return SNN_E_UNSUPPORTED;
+}
 
 template <int IO, int V, typename F>
 snn_status chunk_variant(const Plan& p, F&& f) {

@@ -521,8 +521,15 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
     if (v_last != nullptr && (ALL || active)) store_f32<V>(v_last + n0, v);
 }
 
-// Grid: one lane per V neurons over ceil(max(N, 8*row_bytes) / V) lanes.  Lanes at or beyond
-// N load nothing and report no spikes; they exist only to complete spike-bit words.
+// Whether a lane at or beyond N must stay: to complete the spike-bit words of the lanes
+// before it.  Any other lane leaves at once, and the rest of a partial workgroup runs the
+// unguarded path: per-lane guards put every load under a branch, and the wait counts behind
+// them made the one partial workgroup of a small layer its slowest by far (fp32, T = 200,
+// N = 2000: forward 24.9 -> 11.8 us).
+template <int SPK, int V>
+constexpr bool pads_words() { return SPK == SNN_SPK_BITS && V > 1; }
+
+// Grid: one lane per V neurons over ceil(max(N, 8*row_bytes) / V) lanes.
 // BLK: the workgroup size; above kBlock (layers of several chunks, not double-buffered)
 // the waves of a workgroup that lies wholly inside N meet at a barrier after every chunk.
 template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock>
@@ -534,42 +541,42 @@ __global__ __launch_bounds__(BLK) void lif_forward_kernel(LifK c, int64_t T, int
                                                           float* __restrict__ v_out,
                                                           const float* __restrict__ v_in,
                                                           float* __restrict__ v_last) {
-    static_assert(BLK == kBlock || !PIPE, "barriers only in the single-buffered chunk loop");
+    static_assert(BLK <= kBlock || !PIPE, "barriers only in the single-buffered chunk loop");
     const int64_t first = xcd_contiguous_block() * BLK * V;
     const int64_t n0 = first + int64_t(threadIdx.x) * V;
     const DenseIn<IO, V> in{x};
-    if (first + BLK * V <= N)
+    if (first + BLK * V <= N) {
         forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, true, DenseIn<IO, V>, (BLK > kBlock)>(
             c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
-    else
-        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, false>(c, in, T, N, n0, spikes, row_bytes, saved, v_out,
-                                                               v_in, v_last);
+    } else if (pads_words<SPK, V>() || n0 < N) {
+        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, !pads_words<SPK, V>()>(
+            c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
+    }
 }
 
 // The same forward with the input current read from the previous layer's spikes through
 // the per-feature gain (neuron n has feature n % F).  Spikes in and out share the format.
-// Its chunks are single-buffered: a spike word per lane and row is too little to hide
-// behind a second buffer's registers.
-template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT>
-__global__ __launch_bounds__(kBlock) void lif_forward_gain_kernel(LifK c, int64_t T, int64_t N, int64_t F,
-                                                                  const uint8_t* __restrict__ spikes_in,
-                                                                  const float* __restrict__ gain,
-                                                                  uint8_t* __restrict__ spikes,
-                                                                  int64_t row_bytes,
-                                                                  float* __restrict__ saved,
-                                                                  float* __restrict__ v_out) {
-    const int64_t first = xcd_contiguous_block() * kBlock * V;
+template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE = false, int BLK = kBlock>
+__global__ __launch_bounds__(BLK) void lif_forward_gain_kernel(LifK c, int64_t T, int64_t N, int64_t F,
+                                                               const uint8_t* __restrict__ spikes_in,
+                                                               const float* __restrict__ gain,
+                                                               uint8_t* __restrict__ spikes,
+                                                               int64_t row_bytes,
+                                                               float* __restrict__ saved,
+                                                               float* __restrict__ v_out) {
+    const int64_t first = xcd_contiguous_block() * BLK * V;
     const int64_t n0 = first + int64_t(threadIdx.x) * V;
     GainSpikeIn<IO, SPK, V> in;
     in.s = spikes_in;
     in.row_bytes = row_bytes;
     in.init(gain, F, n0, n0 < N);
-    if (first + kBlock * V <= N)
-        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, false, true>(c, in, T, N, n0, spikes, row_bytes, saved, v_out,
-                                                              nullptr, nullptr);
-    else
-        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, false, false>(c, in, T, N, n0, spikes, row_bytes, saved, v_out,
-                                                               nullptr, nullptr);
+    if (first + BLK * V <= N) {
+        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, true>(c, in, T, N, n0, spikes, row_bytes, saved, v_out,
+                                                                  nullptr, nullptr);
+    } else if (pads_words<SPK, V>() || n0 < N) {
+        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, !pads_words<SPK, V>()>(
+            c, in, T, N, n0, spikes, row_bytes, saved, v_out, nullptr, nullptr);
+    }
 }
 
 // Backward of one chunk.  v/y enter as the state before the chunk's first step; g enters
@@ -772,6 +779,133 @@ __global__ __launch_bounds__(kBlock) void lif_backward_gain_kernel(LifK c, int64
     in.row_bytes = row_bytes;
     in.init(gain, F, n0, true);
     backward_lanes<IO, RESET, V, K, false, true>(c, in, T, N, n0, saved, gs, gs_in, BwdSeg{nullptr, nullptr, nullptr});
+}
+
+// ------------------------------------------------------------------------------------
+// The backward of a layer of few neurons and many steps.  Its lanes are too few to hide any
+// latency, and walking the chunks one after the other leaves the chip waiting on a chain of
+// loads, recomputes and surrogates, one chunk at a time.  Only g itself is a chain through
+// time: each chunk's membranes follow from its own checkpoint.  So the waves of a workgroup
+// share 64 neurons (one per lane) and take the chunks in turn, last first: every wave loads
+// its chunk, recomputes it and forms delta and dv'/dv of its steps at any time, then waits
+// for its turn, takes g from the wave before it through LDS, runs the two dependent
+// operations per step that are left, and hands g on before it stores.  The operations on a
+// value are those of backward_rows in their order, so the results are the same bit for bit.
+// The wait ends because the wave waited for is of the same workgroup (resident with it) and
+// itself waits only for earlier turns.  Per wave the three values of a step are pinned in
+// registers before the wait (the compiler otherwise moves the surrogate behind it, into the
+// chain: 48 instead of 25 us).
+// Measured, fp32, against double-buffered chunks of 2 neurons per lane: x[1000][8192] 122 ->
+// 25 us, [1000][2000] 131 -> 21 us, [40][8192] 8.6 -> 3.4 us, [200][65536] 38.8 -> 30.9 us,
+// [200][98304] 44.6 -> 46.6 us.
+constexpr int kRelayWaves = 8;
+
+template <int IO, int RESET, int K, bool GAIN, typename In>
+__device__ __forceinline__ void backward_relay(const LifK& c, const In& in, int64_t T, int64_t N, int64_t n0,
+                                               const float* __restrict__ saved, const void* gs, void* gx,
+                                               const BwdSeg& seg, float (&g_slot)[2][kWave], int& turn) {
+    using Io = IoVec<IO, 1>;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), waves = blockDim.x / kWave;
+    const int64_t chunks = (T + K - 1) / K;
+    // turn i is chunk chunks - 1 - i; rows at and beyond kn (tail chunk) repeat row kn - 1 in
+    // the loads and leave g alone
+    auto take = [&](int64_t i, int kn, auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        const int64_t ch = chunks - 1 - i, t0 = ch * K;
+        const float* vp = ch > 0 ? saved + (ch - 1) * N : seg.v_in;
+        float v = c.rest;
+        if (vp != nullptr) v = ld_nt<float>(vp + n0);
+        typename In::raw xr[K];
+        typename Io::raw gr[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) xr[k] = in.load(N, t0 + (FULL || k < kn ? k : kn - 1), n0);
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) gr[k] = Io::load(gs, (t0 + (FULL || k < kn ? k : kn - 1)) * N + n0);
+        bool y = vp != nullptr && v >= c.th;
+        float d[K], dv_next[K], gy[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            lif_step<RESET>(c, v, y, in.get(xr[k], 0, n0));
+            d[k] = surrogate(c, v - c.th);
+            if (RESET == SNN_RESET_HARD)  // k (1 - y^t) + (V_rest - k v^t) delta^t
+                dv_next[k] = fmaf(fmaf(-c.k, v, c.rest), d[k], v >= c.th ? 0.0f : c.k);
+            else                          // k (1 - V_th delta^t)
+                dv_next[k] = fmaf(-c.kth, d[k], c.k);
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            gy[k] = Io::get(gr[k], 0);
+            asm volatile("" : "+v"(d[k]), "+v"(dv_next[k]), "+v"(gy[k]));
+        }
+        float g;
+        if (i == 0) {
+            g = seg.g_in != nullptr ? ld_nt<float>(seg.g_in + n0) : 0.0f;
+        } else {
+            while (__hip_atomic_load(&turn, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != int(i))
+                __builtin_amdgcn_s_sleep(1);
+            g = g_slot[i & 1][lane];
+        }
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) {
+            const float g_k = fmaf(gy[k], d[k], dv_next[k] * g);
+            g = FULL || k < kn ? g_k : g;
+            d[k] = g;
+        }
+        g_slot[(i + 1) & 1][lane] = g;   // last read in turn i - 1
+        __hip_atomic_store(&turn, int(i) + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) {
+            if (FULL || k < kn) {
+                float out[1];
+                if constexpr (GAIN) out[0] = in.gx[0] * d[k];
+                else out[0] = d[k];
+                Io::store(gx, (t0 + k) * N + n0, out);
+            }
+        }
+        if (ch == 0 && seg.g_out != nullptr) st_nt(seg.g_out + n0, g);
+    };
+    int64_t i = wave;
+    const int tail = int(T % K);
+    if (i == 0 && tail) {
+        take(0, tail, std::false_type{});
+        i += waves;
+    }
+    for (; i < chunks; i += waves) take(i, K, std::true_type{});
+}
+
+// Grid: one workgroup of up to kRelayWaves waves per 64 neurons.
+template <int IO, int RESET, int K>
+__global__ __launch_bounds__(kRelayWaves * kWave) void lif_backward_relay_kernel(LifK c, int64_t T, int64_t N,
+                                                                                const void* __restrict__ x,
+                                                                                const float* __restrict__ saved,
+                                                                                const void* gs, void* gx,
+                                                                                BwdSeg seg) {
+    __shared__ float g_slot[2][kWave];
+    __shared__ int turn;
+    if (threadIdx.x == 0) turn = 0;
+    __syncthreads();
+    const int64_t n0 = xcd_contiguous_block() * kWave + (threadIdx.x & (kWave - 1));
+    if (n0 >= N) return;
+    backward_relay<IO, RESET, K, false>(c, DenseIn<IO, 1>{x}, T, N, n0, saved, gs, gx, seg, g_slot, turn);
+}
+
+template <int IO, int SPK, int RESET, int K>
+__global__ __launch_bounds__(kRelayWaves * kWave) void lif_backward_gain_relay_kernel(
+    LifK c, int64_t T, int64_t N, int64_t F, const uint8_t* __restrict__ spikes_in, const float* __restrict__ gain,
+    int64_t row_bytes, const float* __restrict__ saved, const void* gs, void* gs_in) {
+    __shared__ float g_slot[2][kWave];
+    __shared__ int turn;
+    if (threadIdx.x == 0) turn = 0;
+    __syncthreads();
+    const int64_t n0 = xcd_contiguous_block() * kWave + (threadIdx.x & (kWave - 1));
+    if (n0 >= N) return;
+    GainSpikeIn<IO, SPK, 1> in;
+    in.s = spikes_in;
+    in.row_bytes = row_bytes;
+    in.init(gain, F, n0, true);
+    backward_relay<IO, RESET, K, true>(c, in, T, N, n0, saved, gs, gs_in, BwdSeg{nullptr, nullptr, nullptr}, g_slot,
+                                       turn);
 }
 
 // ------------------------------------------------------------------------------------
