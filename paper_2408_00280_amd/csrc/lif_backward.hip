@@ -38,6 +38,22 @@ snn_status backward_entry(int reset, const Plan& p, const LifK& k, int64_t T, in
                                   N, x, sv, gs, gx, seg);
             });
         }
+        if constexpr (IO == SNN_IO_BF16) {
+            auto ragged = [&](auto V, auto K, auto blk) {
+                constexpr int R = decltype(rst)::value, B = decltype(blk)::value;
+                constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
+                const dim3 g = wide_grid<SNN_SPK_IO, Vc>(N, B);
+                if constexpr (B == kSyncBlock) {
+                    if (p.syncb)
+                        return launch_blk(lif_backward_kernel<IO, R, Vc, Kc, false, B, true, true>, g, B, s, k, T, N, x,
+                                          sv, gs, gx, seg);
+                }
+                return launch_blk(lif_backward_kernel<IO, R, Vc, Kc, false, B, false, true>, g, B, s, k, T, N, x, sv,
+                                  gs, gx, seg);
+            };
+            if (p.rb == 4) return ragged_variant<4>(p, T, N, ragged);
+            if (p.rb == 2) return ragged_variant<2>(p, T, N, ragged);
+        }
         return backward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
             constexpr int R = decltype(rst)::value;
             constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
@@ -45,7 +61,7 @@ snn_status backward_entry(int reset, const Plan& p, const LifK& k, int64_t T, in
             auto run = [&](auto blk, auto sync) {
                 constexpr int B = decltype(blk)::value;
                 constexpr bool S = decltype(sync)::value;
-                return launch_blk(lif_backward_kernel<IO, R, Vc, Kc, Pc, B, S>, grid_for((N + Vc - 1) / Vc, B), B, s,
+                return launch_blk(lif_backward_kernel<IO, R, Vc, Kc, Pc, B, S>, wide_grid<SNN_SPK_IO, Vc>(N, B), B, s,
                                   k, T, N, x, sv, gs, gx, seg);
             };
             if constexpr (!Pc && Vc == 2) {

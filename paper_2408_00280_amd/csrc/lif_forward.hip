@@ -26,12 +26,26 @@ snn_status forward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int
         if (p.narrow) {
             return narrow_variant(p, [&](auto K) {
                 constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
-                const dim3 g = grid_for(p.lanes * p.vf, kWave);
+                const dim3 g = grid_for(N, kWave);
                 return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, 1, Kc, Kc, true, true, kWave>, g, kWave, s, k,
                                           T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last)
                              : launch_blk(lif_forward_kernel<IO, SPK, R, 1, Kc, Kc, false, true, kWave>, g, kWave, s, k,
                                           T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last);
             });
+        }
+        if constexpr (IO == SNN_IO_BF16) {
+            auto ragged = [&](auto V, auto K, auto blk) {
+                constexpr int R = decltype(rst)::value, B = decltype(blk)::value;
+                constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value, FB = forward_batch(IO, Vc, Kc, false);
+                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, true, false, B, true>,
+                                          wide_grid<SPK, Vc>(N, B), B, s, k, T, N, x, sp, p.row_bytes, sv, v_out, v_in,
+                                          v_last)
+                             : launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, false, false, B, true>,
+                                          wide_grid<SPK, Vc>(N, B), B, s, k, T, N, x, sp, p.row_bytes, sv, v_out, v_in,
+                                          v_last);
+            };
+            if (p.rf == 8) return ragged_variant<8>(p, T, N, ragged);
+            if (p.rf == 2) return ragged_variant<2>(p, T, N, ragged);
         }
         return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
             constexpr int R = decltype(rst)::value;
@@ -40,7 +54,7 @@ snn_status forward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int
             constexpr int FB = forward_batch(IO, Vc, Kc, Pc);
             auto run = [&](auto blk) {
                 constexpr int B = decltype(blk)::value;
-                const dim3 g = grid_for(p.lanes, B);
+                const dim3 g = wide_grid<SPK, Vc>(N, B);
                 return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, true, Pc, B>, g, B, s, k, T, N,
                                           x, sp, p.row_bytes, sv, v_out, v_in, v_last)
                              : launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, false, Pc, B>, g, B, s, k, T, N,
@@ -68,12 +82,11 @@ snn_status forward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t T
     const uint8_t* si = static_cast<const uint8_t*>(spikes_in);
     uint8_t* sp = static_cast<uint8_t*>(spikes);
     float* sv = static_cast<float*>(saved);
-    const dim3 g = grid_for(p.lanes);
     auto go = [&](auto rst) {
         if (p.narrow) {
             return narrow_variant(p, [&](auto K) {
                 constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
-                const dim3 gn = grid_for(p.lanes * p.vf, kWave);
+                const dim3 gn = grid_for(N, kWave);
                 return v_out ? launch_blk(lif_forward_gain_kernel<IO, SPK, R, 1, Kc, Kc, true, true, kWave>, gn, kWave,
                                           s, k, T, N, F, si, gain, sp, p.row_bytes, sv, v_out)
                              : launch_blk(lif_forward_gain_kernel<IO, SPK, R, 1, Kc, Kc, false, true, kWave>, gn, kWave,
@@ -87,6 +100,7 @@ snn_status forward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t T
                 return SNN_E_UNSUPPORTED;   // the gain-fed layer's plan never double-buffers
             } else {
                 constexpr int FB = forward_batch(IO, Vc, Kc, false);
+                const dim3 g = wide_grid<SPK, Vc>(N);
                 return v_out ? launch(lif_forward_gain_kernel<IO, SPK, R, Vc, FB, Kc, true>, g, s, k, T, N, F, si,
                                       gain, sp, p.row_bytes, sv, v_out)
                              : launch(lif_forward_gain_kernel<IO, SPK, R, Vc, FB, Kc, false>, g, s, k, T, N, F,

@@ -51,6 +51,8 @@ struct Plan {
     int blkf;        // workgroup sizes of the dense forward and backward kernels
     int blkb;
     bool syncb;      // the backward's kSyncBlock workgroups meet at a barrier after each chunk
+    int rf;          // bf16 layers whose N is not a multiple of the widths above: the wider
+    int rb;          // lanes that take their place, all but a rest of N (else 0)
     bool narrow;     // few neurons, several chunks: one neuron per lane in place of vf and vb,
                      // the forward in one-wave workgroups, the backward as a relay of waves
     int64_t lanes;   // lanes in the forward grid
@@ -124,6 +126,19 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     p.blkb = long_walk && p.vb == 2 ? kSyncBlock : kBlock;
     p.syncb = c->io == SNN_IO_F32 || (T + p.k - 1) / p.k <= kSyncBf16Chunks;
     p.narrow = T > p.k && N <= kNarrowN;
+    // bf16 rows are read 2 (large layers 8 and 4) neurons per lane whatever N is, a vector
+    // needing only its elements' alignment; 2-byte loads, and chunks of 32 single neurons
+    // whose tail waits at every row, cost far more than unaligned vectors: forward / backward
+    // of x[20][1010625] 25.3 -> 20.8 / 96.8 -> 30.0 us, [40][300001] 22.0 -> 15.0 / 66.7 -> 21.0
+    // us, [17][3897755] (bit spikes) 50.2 -> 28.1 / 314 -> 88.6 us, [64][4000002] (bit spikes,
+    // 8 instead of 2 per lane forward) 139 -> 112 us.  fp32 rows of odd N keep one neuron, a
+    // dword, per lane.
+    p.rf = p.rb = 0;
+    if (c->io == SNN_IO_BF16 && !p.narrow) {
+        const int wf = N / 8 >= kFillLanes ? 8 : 2, wb = T <= 16 && N / 4 >= kFillLanes ? 4 : 2;
+        p.rf = wf > p.vf ? wf : 0;
+        p.rb = wb > p.vb ? wb : 0;
+    }
     p.row_bytes = spike_row_bytes(c, N);
     const int64_t covered = c->spk == SNN_SPK_BITS ? p.row_bytes * 8 : N;
     p.lanes = (covered + p.vf - 1) / p.vf;
@@ -202,6 +217,13 @@ inline LifK kernel_consts(const snn_lif_cfg* c) {
 
 inline dim3 grid_for(int64_t lanes, int blk = kBlock) { return dim3(unsigned((lanes + blk - 1) / blk)); }
 
+// V-wide lanes over the whole vectors of N, and a workgroup for the rest, if any.
+template <int SPK, int V>
+dim3 wide_grid(int64_t N, int blk = kBlock) {
+    const int64_t whole = whole_vectors<SPK, V>(N);
+    return dim3(unsigned((whole / V + blk - 1) / blk + (whole < N)));
+}
+
 template <typename Tuple, size_t... I>
 void fill_argv(Tuple& t, void** argv, std::index_sequence<I...>) {
     ((argv[I] = static_cast<void*>(&std::get<I>(t))), ...);
@@ -224,6 +246,9 @@ snn_status launch(void (*kernel)(P...), dim3 grid, hipStream_t stream, A... a) {
     return launch_blk(kernel, grid, kBlock, stream, a...);
 }
 
+template <int I>
+using IntC = std::integral_constant<int, I>;
+
 // Rows per load batch of the forward.  The forward never revisits a row, so it need not
 // hold a whole 32-step chunk (the checkpoint interval) in registers: it loads 16 rows at a
 // time and checkpoints after every second batch.
@@ -231,12 +256,32 @@ constexpr int forward_batch(int io, int v, int k, bool pipe) {
     return (!pipe && k > 16) ? 16 : k;
 }
 
+// Ragged layers (bf16): V neurons per lane, single-buffered chunks of the plan's length, in
+// kSyncBlock workgroups where layers of their size take them.
+template <int V, int K, typename F>
+snn_status ragged_blocks(bool sync_block, F&& f) {
+    if constexpr (K == 32) {
+        if (sync_block) return f(IntC<V>{}, IntC<K>{}, IntC<kSyncBlock>{});
+    }
+    return f(IntC<V>{}, IntC<K>{}, IntC<kBlock>{});
+}
+
+template <int V, typename F>
+snn_status ragged_variant(const Plan& p, int64_t T, int64_t N, F&& f) {
+    const bool sync_block = T > p.k && N / 2 >= 4 * kFillLanes;
+    switch (p.k) {
+        case 4: return ragged_blocks<V, 4>(sync_block, f);
+        case 8: return ragged_blocks<V, 8>(sync_block, f);
+        case 16: return ragged_blocks<V, 16>(sync_block, f);
+        case 32: if constexpr (V != 4) return ragged_blocks<V, 32>(sync_block, f);
+                 break;
+    }
+    return SNN_E_UNSUPPORTED;
+}
+
 // Calls f(V, K, PIPE) -- std::integral_constant / bool_constant tags -- with the lane width
 // and chunk length the plan chose for the forward (vf) or the backward (vb): the
 // combinations a kernel translation unit instantiates.
-template <int I>
-using IntC = std::integral_constant<int, I>;
-
 // The chunk lengths of a narrow layer: those of the plans of 2 neurons (even N) and of 1.
 template <typename F>
 snn_status narrow_variant(const Plan& p, F&& f) {

@@ -37,14 +37,24 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-template <typename E>
+// A vector access needs only the alignment A of its elements (global memory takes unaligned
+// vectors on gfx9; the instruction is the same), so a row may start at any element.
+template <typename E, int A = 4>
 __device__ __forceinline__ E ld_nt(const void* p) {
-    return __builtin_nontemporal_load(static_cast<const E*>(p));
+    typedef E EU __attribute__((aligned(A)));
+    return __builtin_nontemporal_load(static_cast<const EU*>(p));
+}
+
+template <int A = 4, typename E>
+__device__ __forceinline__ void st_nt(void* p, E v) {
+    typedef E EU __attribute__((aligned(A)));
+    __builtin_nontemporal_store(v, static_cast<EU*>(p));
 }
 
 template <typename E>
-__device__ __forceinline__ void st_nt(void* p, E v) {
-    __builtin_nontemporal_store(v, static_cast<E*>(p));
+__device__ __forceinline__ void st_bytes(uint8_t* p, E v) {   // an ordinary store at any byte
+    typedef E EU __attribute__((aligned(1)));
+    *reinterpret_cast<EU*>(p) = v;
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs (workgroup b runs on XCD b % 8).
@@ -114,43 +124,43 @@ __device__ __forceinline__ float io_round(float f) {
 template <>
 struct IoVec<SNN_IO_BF16, 8> {
     using raw = u32x4_t;
-    __device__ static raw load(const void* b, int64_t i) { return ld_nt<raw>(static_cast<const uint16_t*>(b) + i); }
+    __device__ static raw load(const void* b, int64_t i) { return ld_nt<raw, 2>(static_cast<const uint16_t*>(b) + i); }
     __device__ static float get(const raw& r, int j) { return (j & 1) ? bf16_hi(r[j >> 1]) : bf16_lo(r[j >> 1]); }
     __device__ static void store(void* b, int64_t i, const float (&f)[8]) {
         const raw w = {pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]),
                        pack_bf16x2(f[6], f[7])};
-        st_nt(static_cast<uint16_t*>(b) + i, w);
+        st_nt<2>(static_cast<uint16_t*>(b) + i, w);
     }
 };
 
 template <>
 struct IoVec<SNN_IO_BF16, 4> {
     using raw = u32x2_t;
-    __device__ static raw load(const void* b, int64_t i) { return ld_nt<raw>(static_cast<const uint16_t*>(b) + i); }
+    __device__ static raw load(const void* b, int64_t i) { return ld_nt<raw, 2>(static_cast<const uint16_t*>(b) + i); }
     __device__ static float get(const raw& r, int j) { return (j & 1) ? bf16_hi(r[j >> 1]) : bf16_lo(r[j >> 1]); }
     __device__ static void store(void* b, int64_t i, const float (&f)[4]) {
         const raw w = {pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3])};
-        st_nt(static_cast<uint16_t*>(b) + i, w);
+        st_nt<2>(static_cast<uint16_t*>(b) + i, w);
     }
 };
 
 template <>
 struct IoVec<SNN_IO_BF16, 2> {
     using raw = uint32_t;
-    __device__ static raw load(const void* b, int64_t i) { return ld_nt<raw>(static_cast<const uint16_t*>(b) + i); }
+    __device__ static raw load(const void* b, int64_t i) { return ld_nt<raw, 2>(static_cast<const uint16_t*>(b) + i); }
     __device__ static float get(const raw& r, int j) { return j ? bf16_hi(r) : bf16_lo(r); }
     __device__ static void store(void* b, int64_t i, const float (&f)[2]) {
-        st_nt(static_cast<uint16_t*>(b) + i, pack_bf16x2(f[0], f[1]));
+        st_nt<2>(static_cast<uint16_t*>(b) + i, pack_bf16x2(f[0], f[1]));
     }
 };
 
 template <>
 struct IoVec<SNN_IO_BF16, 1> {
     using raw = uint16_t;
-    __device__ static raw load(const void* b, int64_t i) { return ld_nt<raw>(static_cast<const uint16_t*>(b) + i); }
+    __device__ static raw load(const void* b, int64_t i) { return ld_nt<raw, 2>(static_cast<const uint16_t*>(b) + i); }
     __device__ static float get(const raw& r, int) { return __uint_as_float(uint32_t(r) << 16); }
     __device__ static void store(void* b, int64_t i, const float (&f)[1]) {
-        st_nt(static_cast<uint16_t*>(b) + i, static_cast<uint16_t>(pack_bf16x2(f[0], 0.0f) & 0xffffu));
+        st_nt<2>(static_cast<uint16_t*>(b) + i, static_cast<uint16_t>(pack_bf16x2(f[0], 0.0f) & 0xffffu));
     }
 };
 
@@ -190,7 +200,7 @@ struct SpikeFmt<SNN_SPK_U8, 4> {
                                  const bool (&y)[4]) {
         const uint32_t w = uint32_t(y[0]) | (uint32_t(y[1]) << 8) | (uint32_t(y[2]) << 16) |
                            (uint32_t(y[3]) << 24);
-        if (active) *reinterpret_cast<uint32_t*>(s + t * row_bytes + n0) = w;
+        if (active) st_bytes(s + t * row_bytes + n0, w);
     }
 };
 
@@ -198,10 +208,9 @@ template <>
 struct SpikeFmt<SNN_SPK_U8, 8> {
     __device__ static void store(uint8_t* s, int64_t row_bytes, int64_t t, int64_t n0, bool active,
                                  const bool (&y)[8]) {
-        uint2 w;
-        w.x = uint32_t(y[0]) | (uint32_t(y[1]) << 8) | (uint32_t(y[2]) << 16) | (uint32_t(y[3]) << 24);
-        w.y = uint32_t(y[4]) | (uint32_t(y[5]) << 8) | (uint32_t(y[6]) << 16) | (uint32_t(y[7]) << 24);
-        if (active) *reinterpret_cast<uint2*>(s + t * row_bytes + n0) = w;
+        const u32x2_t w = {uint32_t(y[0]) | (uint32_t(y[1]) << 8) | (uint32_t(y[2]) << 16) | (uint32_t(y[3]) << 24),
+                           uint32_t(y[4]) | (uint32_t(y[5]) << 8) | (uint32_t(y[6]) << 16) | (uint32_t(y[7]) << 24)};
+        if (active) st_bytes(s + t * row_bytes + n0, w);
     }
 };
 
@@ -209,7 +218,7 @@ template <>
 struct SpikeFmt<SNN_SPK_U8, 2> {
     __device__ static void store(uint8_t* s, int64_t row_bytes, int64_t t, int64_t n0, bool active,
                                  const bool (&y)[2]) {
-        if (active) *reinterpret_cast<uint16_t*>(s + t * row_bytes + n0) = (uint16_t(uint32_t(y[0]) | (uint32_t(y[1]) << 8)));
+        if (active) st_bytes(s + t * row_bytes + n0, uint16_t(uint32_t(y[0]) | (uint32_t(y[1]) << 8)));
     }
 };
 
@@ -339,10 +348,10 @@ __device__ __forceinline__ void load_f32(const float* p, float (&f)[V]) {
 // On gfx9-family GPUs one in-order counter (vmcnt) covers every outstanding vector load
 // AND store, and the compiler's wait before a use is only as precise as the control flow
 // allows: a load or store under a branch makes the merged count conservative, and then a
-// wait for an old row also waits for younger loads.  So: workgroups whose lanes are all in
-// range run a path with no per-lane guards (ALL = true), checkpoint loads are issued before
-// the row loads they precede in use, and double-buffered loops peel their first iteration
-// so that the loop body issues every load unconditionally.
+// wait for an old row also waits for younger loads.  So: no load or store of a lane is
+// guarded (whole_vectors), checkpoint loads are issued before the row loads they precede in
+// use, and double-buffered loops peel their first iteration so that the loop body issues
+// every load unconditionally.
 //
 // Where the input current comes from is a policy:
 //   DenseIn     -- x[T][N] in the I/O dtype (a layer fed by an ANN operator);
@@ -367,9 +376,9 @@ struct GainSpikeIn {
     const uint8_t* s;
     int64_t row_bytes;
     float gx[V];   // gain of the lane's neurons, rounded to the I/O dtype
-    __device__ void init(const float* gain, int64_t F, int64_t n0, bool active) {
+    __device__ void init(const float* gain, int64_t F, int64_t n0) {
 #pragma unroll
-        for (int j = 0; j < V; ++j) gx[j] = io_round<IO>(active ? gain[(n0 + j) % F] : 0.0f);
+        for (int j = 0; j < V; ++j) gx[j] = io_round<IO>(gain[(n0 + j) % F]);
     }
     __device__ raw load(int64_t N, int64_t t, int64_t n0) const {
         if constexpr (SPK == SNN_SPK_IO) {
@@ -408,19 +417,18 @@ __device__ __forceinline__ void load_rows(const In& in, typename In::raw (&buf)[
     }
 }
 
-template <int IO, int SPK, int RESET, int V, int K, bool VOUT, bool FULL, bool ALL, typename In>
+template <int IO, int SPK, int RESET, int V, int K, bool VOUT, bool FULL, typename In>
 __device__ __forceinline__ void forward_rows(const LifK& c, const In& in, const typename In::raw (&xr)[K], int64_t N,
-                                             int64_t t0, int kn, int64_t n0, bool active,
-                                             uint8_t* __restrict__ spikes, int64_t row_bytes,
-                                             float* __restrict__ v_out, float (&v)[V], bool (&y)[V]) {
-    const bool on = ALL || active;
+                                             int64_t t0, int kn, int64_t n0, uint8_t* __restrict__ spikes,
+                                             int64_t row_bytes, float* __restrict__ v_out, float (&v)[V],
+                                             bool (&y)[V]) {
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         if (FULL || i < kn) {
 #pragma unroll
-            for (int j = 0; j < V; ++j) lif_step<RESET>(c, v[j], y[j], on ? in.get(xr[i], j, n0) : 0.0f);
-            SpikeOut<IO, SPK, V>::store(spikes, row_bytes, t0 + i, n0, on, y);
-            if (VOUT && on) store_f32<V>(v_out + (t0 + i) * N + n0, v);
+            for (int j = 0; j < V; ++j) lif_step<RESET>(c, v[j], y[j], in.get(xr[i], j, n0));
+            SpikeOut<IO, SPK, V>::store(spikes, row_bytes, t0 + i, n0, true, y);
+            if (VOUT) store_f32<V>(v_out + (t0 + i) * N + n0, v);
         }
     }
 }
@@ -434,14 +442,12 @@ __device__ __forceinline__ void forward_rows(const LifK& c, const In& in, const 
 // Segment state (a sequence split along time): v_in, if not null, is the membrane the
 // previous segment ended with, and the spike state entering the first step is v_in >= V_th;
 // v_last, if not null, receives the membrane after the last step.
-template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, bool ALL, typename In,
-          bool SYNC = false>
+template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, typename In, bool SYNC = false>
 __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64_t T, int64_t N, int64_t n0,
                                               uint8_t* __restrict__ spikes, int64_t row_bytes,
                                               float* __restrict__ saved, float* __restrict__ v_out,
                                               const float* __restrict__ v_in, float* __restrict__ v_last) {
     using raw = typename In::raw;
-    const bool active = ALL || n0 < N;
     float v[V];
     bool y[V];
 #pragma unroll
@@ -449,7 +455,7 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
         v[j] = c.rest;  // v^0 = V_rest
         y[j] = false;   // no spike before the first step
     }
-    if (v_in != nullptr && (ALL || active)) {
+    if (v_in != nullptr) {
         load_f32<V>(v_in + n0, v);
 #pragma unroll
         for (int j = 0; j < V; ++j) y[j] = v[j] >= c.th;
@@ -462,19 +468,18 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
     // and back-edge and make the compiler's waits conservative.
     auto load = [&](raw (&buf)[K], int64_t ch) {
         __builtin_amdgcn_sched_barrier(0);
-        if (ALL || active) load_rows<In, K, true, false>(in, buf, N, ch * K, K, n0);
+        load_rows<In, K, true, false>(in, buf, N, ch * K, K, n0);
         __builtin_amdgcn_sched_barrier(0);
     };
     static_assert(KC % K == 0 && (!PIPE || KC == K), "checkpoint interval");
     // ckpt: true_type = this chunk is never the last (checkpoint unconditionally)
     auto step = [&](const raw (&buf)[K], int64_t ch, auto ckpt) {
-        forward_rows<IO, SPK, RESET, V, K, VOUT, true, ALL>(c, in, buf, N, ch * K, K, n0, active, spikes, row_bytes,
-                                                            v_out, v, y);
+        forward_rows<IO, SPK, RESET, V, K, VOUT, true>(c, in, buf, N, ch * K, K, n0, spikes, row_bytes, v_out, v, y);
         if constexpr (KC == K) {
-            if ((decltype(ckpt)::value || ch < last) && (ALL || active)) store_f32<V>(saved + ch * N + n0, v);
+            if (decltype(ckpt)::value || ch < last) store_f32<V>(saved + ch * N + n0, v);
         } else {
             const int64_t t_end = (ch + 1) * K;
-            if (t_end % KC == 0 && t_end < T && (ALL || active)) store_f32<V>(saved + (t_end / KC - 1) * N + n0, v);
+            if (t_end % KC == 0 && t_end < T) store_f32<V>(saved + (t_end / KC - 1) * N + n0, v);
         }
     };
     constexpr std::true_type not_last{};
@@ -514,25 +519,18 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
         }
     }
     if (k_tail) {
-        if (ALL || active) load_rows<In, K, false, false>(in, a, N, n_full * K, k_tail, n0);
-        forward_rows<IO, SPK, RESET, V, K, VOUT, false, ALL>(c, in, a, N, n_full * K, k_tail, n0, active, spikes,
-                                                             row_bytes, v_out, v, y);
+        load_rows<In, K, false, false>(in, a, N, n_full * K, k_tail, n0);
+        forward_rows<IO, SPK, RESET, V, K, VOUT, false>(c, in, a, N, n_full * K, k_tail, n0, spikes, row_bytes, v_out,
+                                                        v, y);
     }
-    if (v_last != nullptr && (ALL || active)) store_f32<V>(v_last + n0, v);
+    if (v_last != nullptr) store_f32<V>(v_last + n0, v);
 }
 
-// Whether a lane at or beyond N must stay: to complete the spike-bit words of the lanes
-// before it.  Any other lane leaves at once, and the rest of a partial workgroup runs the
-// unguarded path: per-lane guards put every load under a branch, and the wait counts behind
-// them made the one partial workgroup of a small layer its slowest by far (fp32, T = 200,
-// N = 2000: forward 24.9 -> 11.8 us).
-template <int SPK, int V>
-constexpr bool pads_words() { return SPK == SNN_SPK_BITS && V > 1; }
-
-// Grid: one lane per V neurons over ceil(max(N, 8*row_bytes) / V) lanes.
+// Grid: one lane per V neurons of whole_vectors, and a workgroup for the rest (wide_grid).
 // BLK: the workgroup size; above kBlock (layers of several chunks, not double-buffered)
 // the waves of a workgroup that lies wholly inside N meet at a barrier after every chunk.
-template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock>
+// RAGGED: N need not be a multiple of V.
+template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock, bool RAGGED = false>
 __global__ __launch_bounds__(BLK) void lif_forward_kernel(LifK c, int64_t T, int64_t N,
                                                           const void* __restrict__ x,
                                                           uint8_t* __restrict__ spikes,
@@ -542,16 +540,29 @@ __global__ __launch_bounds__(BLK) void lif_forward_kernel(LifK c, int64_t T, int
                                                           const float* __restrict__ v_in,
                                                           float* __restrict__ v_last) {
     static_assert(BLK <= kBlock || !PIPE, "barriers only in the single-buffered chunk loop");
-    const int64_t first = xcd_contiguous_block() * BLK * V;
-    const int64_t n0 = first + int64_t(threadIdx.x) * V;
-    const DenseIn<IO, V> in{x};
-    if (first + BLK * V <= N) {
-        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, true, DenseIn<IO, V>, (BLK > kBlock)>(
-            c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
-    } else if (pads_words<SPK, V>() || n0 < N) {
-        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, !pads_words<SPK, V>()>(
-            c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
+    constexpr bool REST = RAGGED || has_rest<SPK, V>();
+    const int64_t whole = REST ? whole_vectors<SPK, V>(N) : N;
+    int64_t block = xcd_contiguous_block();
+    if constexpr (REST) {
+        if (whole < N) {
+            if (block == 0) {
+                const int64_t n0 = whole + threadIdx.x;
+                if (n0 < N)
+                    forward_lanes<IO, SPK, RESET, 1, K, KC, VOUT, PIPE>(c, DenseIn<IO, 1>{x}, T, N, n0, spikes,
+                                                                        row_bytes, saved, v_out, v_in, v_last);
+                return;
+            }
+            --block;
+        }
     }
+    const int64_t first = block * BLK * V, n0 = first + int64_t(threadIdx.x) * V;
+    const DenseIn<IO, V> in{x};
+    if (BLK > kBlock && first + BLK * V <= whole)
+        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, DenseIn<IO, V>, (BLK > kBlock)>(
+            c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
+    else if (n0 < whole)
+        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE>(c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in,
+                                                            v_last);
 }
 
 // The same forward with the input current read from the previous layer's spikes through
@@ -564,19 +575,29 @@ __global__ __launch_bounds__(BLK) void lif_forward_gain_kernel(LifK c, int64_t T
                                                                int64_t row_bytes,
                                                                float* __restrict__ saved,
                                                                float* __restrict__ v_out) {
-    const int64_t first = xcd_contiguous_block() * BLK * V;
-    const int64_t n0 = first + int64_t(threadIdx.x) * V;
-    GainSpikeIn<IO, SPK, V> in;
-    in.s = spikes_in;
-    in.row_bytes = row_bytes;
-    in.init(gain, F, n0, n0 < N);
-    if (first + BLK * V <= N) {
-        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, true>(c, in, T, N, n0, spikes, row_bytes, saved, v_out,
-                                                                  nullptr, nullptr);
-    } else if (pads_words<SPK, V>() || n0 < N) {
-        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, !pads_words<SPK, V>()>(
-            c, in, T, N, n0, spikes, row_bytes, saved, v_out, nullptr, nullptr);
+    constexpr bool REST = has_rest<SPK, V>();
+    const int64_t whole = REST ? whole_vectors<SPK, V>(N) : N;
+    int64_t block = xcd_contiguous_block();
+    if constexpr (REST) {
+        if (whole < N) {
+            if (block == 0) {
+                const int64_t n0 = whole + threadIdx.x;
+                if (n0 >= N) return;
+                GainSpikeIn<IO, SPK, 1> in{spikes_in, row_bytes};
+                in.init(gain, F, n0);
+                forward_lanes<IO, SPK, RESET, 1, K, KC, VOUT, PIPE>(c, in, T, N, n0, spikes, row_bytes, saved, v_out,
+                                                                    nullptr, nullptr);
+                return;
+            }
+            --block;
+        }
     }
+    const int64_t n0 = (block * BLK + threadIdx.x) * V;
+    if (n0 >= whole) return;
+    GainSpikeIn<IO, SPK, V> in{spikes_in, row_bytes};
+    in.init(gain, F, n0);
+    forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE>(c, in, T, N, n0, spikes, row_bytes, saved, v_out, nullptr,
+                                                        nullptr);
 }
 
 // Backward of one chunk.  v/y enter as the state before the chunk's first step; g enters
@@ -743,23 +764,35 @@ __device__ __forceinline__ void backward_lanes(const LifK& c, const In& in, int6
     if (seg.g_out != nullptr) store_f32<V>(seg.g_out + n0, g);
 }
 
-// BLK: the workgroup size.  SYNC: its waves meet at a barrier after every chunk (only in
-// a workgroup wholly inside N; one that is not drops its lanes beyond N).
-template <int IO, int RESET, int V, int K, bool PIPE, int BLK = kBlock, bool SYNC = false>
+// Grid as the forward's.  BLK: the workgroup size.  SYNC: the waves of a workgroup that lies
+// wholly inside N meet at a barrier after every chunk.  RAGGED: N need not be a multiple of V
+// (the rest's code is left out otherwise: merely present, it made the backward of
+// x[16][8388602] 310 -> 350 us, that of [16][8388608] 1% slower).
+template <int IO, int RESET, int V, int K, bool PIPE, int BLK = kBlock, bool SYNC = false, bool RAGGED = false>
 __global__ __launch_bounds__(BLK) void lif_backward_kernel(LifK c, int64_t T, int64_t N,
                                                            const void* __restrict__ x,
                                                            const float* __restrict__ saved,
                                                            const void* gs, void* gx, BwdSeg seg) {
     static_assert(!SYNC || !PIPE, "barriers only in the single-buffered chunk loop");
-    const int64_t first = xcd_contiguous_block() * BLK * V;
-    const int64_t n0 = first + int64_t(threadIdx.x) * V;
-    const DenseIn<IO, V> in{x};
-    if (first + BLK * V <= N) {
-        backward_lanes<IO, RESET, V, K, PIPE, false, DenseIn<IO, V>, SYNC>(c, in, T, N, n0, saved, gs, gx, seg);
-        return;
+    const int64_t whole = RAGGED ? whole_vectors<SNN_SPK_IO, V>(N) : N;
+    int64_t block = xcd_contiguous_block();
+    if constexpr (RAGGED) {
+        if (whole < N) {
+            if (block == 0) {
+                const int64_t n0 = whole + threadIdx.x;
+                if (n0 < N)
+                    backward_lanes<IO, RESET, 1, K, PIPE, false>(c, DenseIn<IO, 1>{x}, T, N, n0, saved, gs, gx, seg);
+                return;
+            }
+            --block;
+        }
     }
-    if (n0 >= N) return;
-    backward_lanes<IO, RESET, V, K, PIPE, false>(c, in, T, N, n0, saved, gs, gx, seg);
+    const int64_t first = block * BLK * V, n0 = first + int64_t(threadIdx.x) * V;
+    const DenseIn<IO, V> in{x};
+    if (SYNC && first + BLK * V <= whole)
+        backward_lanes<IO, RESET, V, K, PIPE, false, DenseIn<IO, V>, SYNC>(c, in, T, N, n0, saved, gs, gx, seg);
+    else if (n0 < whole)
+        backward_lanes<IO, RESET, V, K, PIPE, false>(c, in, T, N, n0, saved, gs, gx, seg);
 }
 
 // Backward of the gain-fed layer: recomputes from the previous layer's spikes and writes
@@ -774,10 +807,8 @@ __global__ __launch_bounds__(kBlock) void lif_backward_gain_kernel(LifK c, int64
     const int64_t first = xcd_contiguous_block() * kBlock * V;
     const int64_t n0 = first + int64_t(threadIdx.x) * V;
     if (first + kBlock * V > N && n0 >= N) return;
-    GainSpikeIn<IO, SPK, V> in;
-    in.s = spikes_in;
-    in.row_bytes = row_bytes;
-    in.init(gain, F, n0, true);
+    GainSpikeIn<IO, SPK, V> in{spikes_in, row_bytes};
+    in.init(gain, F, n0);
     backward_lanes<IO, RESET, V, K, false, true>(c, in, T, N, n0, saved, gs, gs_in, BwdSeg{nullptr, nullptr, nullptr});
 }
 
@@ -900,10 +931,8 @@ __global__ __launch_bounds__(kRelayWaves * kWave) void lif_backward_gain_relay_k
     __syncthreads();
     const int64_t n0 = xcd_contiguous_block() * kWave + (threadIdx.x & (kWave - 1));
     if (n0 >= N) return;
-    GainSpikeIn<IO, SPK, 1> in;
-    in.s = spikes_in;
-    in.row_bytes = row_bytes;
-    in.init(gain, F, n0, true);
+    GainSpikeIn<IO, SPK, 1> in{spikes_in, row_bytes};
+    in.init(gain, F, n0);
     backward_relay<IO, RESET, K, true>(c, in, T, N, n0, saved, gs, gs_in, BwdSeg{nullptr, nullptr, nullptr}, g_slot,
                                        turn);
 }
@@ -920,11 +949,11 @@ template <int V, int L>
 struct StackGains {
     float gx[L - 1][V];   // rounded to the I/O dtype
     template <int IO>
-    __device__ void init(const float* gains, int64_t F, int64_t n0, bool active) {
+    __device__ void init(const float* gains, int64_t F, int64_t n0) {
 #pragma unroll
         for (int l = 0; l < L - 1; ++l) {
 #pragma unroll
-            for (int j = 0; j < V; ++j) gx[l][j] = io_round<IO>(active ? gains[l * F + (n0 + j) % F] : 0.0f);
+            for (int j = 0; j < V; ++j) gx[l][j] = io_round<IO>(gains[l * F + (n0 + j) % F]);
         }
     }
 };
@@ -945,14 +974,13 @@ __device__ __forceinline__ void stack_step(const LifK& c, const StackGains<V, L>
 // Forward of one workgroup's lanes, chunks of K steps (a short tail chunk last).  OUT: also
 // write the hidden layers' spikes (hidden[l][T][row_bytes]) and every layer's membrane
 // (v_out[l][T][N]) where those pointers are not null.
-template <int IO, int SPK, int RESET, int V, int K, int L, bool OUT, bool ALL>
+template <int IO, int SPK, int RESET, int V, int K, int L, bool OUT>
 __device__ __forceinline__ void stack_forward_lanes(const LifK& c, const DenseIn<IO, V>& in,
                                                     const StackGains<V, L>& G, int64_t T, int64_t N, int64_t n0,
                                                     uint8_t* __restrict__ spikes, uint8_t* __restrict__ hidden,
                                                     int64_t row_bytes, float* __restrict__ saved,
                                                     float* __restrict__ v_out) {
     using raw = typename DenseIn<IO, V>::raw;
-    const bool active = ALL || n0 < N;
     float v[L][V];
     bool y[L][V];
 #pragma unroll
@@ -973,17 +1001,17 @@ __device__ __forceinline__ void stack_forward_lanes(const LifK& c, const DenseIn
             if (decltype(full)::value || i < kn) {
                 float x0[V];
 #pragma unroll
-                for (int j = 0; j < V; ++j) x0[j] = active ? in.get(a[i], j, n0) : 0.0f;
+                for (int j = 0; j < V; ++j) x0[j] = in.get(a[i], j, n0);
                 stack_step<RESET, V, L>(c, G, x0, v, y);
                 const int64_t t = t0 + i;
-                SpikeOut<IO, SPK, V>::store(spikes, row_bytes, t, n0, active, y[L - 1]);
+                SpikeOut<IO, SPK, V>::store(spikes, row_bytes, t, n0, true, y[L - 1]);
                 if constexpr (OUT) {
                     if (hidden != nullptr) {
 #pragma unroll
                         for (int l = 0; l < L - 1; ++l)
-                            SpikeOut<IO, SPK, V>::store(hidden + l * T * row_bytes, row_bytes, t, n0, active, y[l]);
+                            SpikeOut<IO, SPK, V>::store(hidden + l * T * row_bytes, row_bytes, t, n0, true, y[l]);
                     }
-                    if (v_out != nullptr && active) {
+                    if (v_out != nullptr) {
 #pragma unroll
                         for (int l = 0; l < L; ++l) store_f32<V>(v_out + (l * T + t) * N + n0, v[l]);
                     }
@@ -993,22 +1021,21 @@ __device__ __forceinline__ void stack_forward_lanes(const LifK& c, const DenseIn
     };
     for (int64_t ch = 0; ch < n_full; ++ch) {
         __builtin_amdgcn_sched_barrier(0);
-        if (active) load_rows<DenseIn<IO, V>, K, true, false>(in, a, N, ch * K, K, n0);
+        load_rows<DenseIn<IO, V>, K, true, false>(in, a, N, ch * K, K, n0);
         __builtin_amdgcn_sched_barrier(0);
         rows(ch * K, K, std::true_type{});
-        if (ch < last && active) {
+        if (ch < last) {
 #pragma unroll
             for (int l = 0; l < L; ++l) store_f32<V>(saved + (ch * L + l) * N + n0, v[l]);
         }
     }
     if (k_tail) {
-        if (active) load_rows<DenseIn<IO, V>, K, false, false>(in, a, N, n_full * K, k_tail, n0);
+        load_rows<DenseIn<IO, V>, K, false, false>(in, a, N, n_full * K, k_tail, n0);
         rows(n_full * K, k_tail, std::false_type{});
     }
 }
 
-// Grid: one lane per V neurons over ceil(max(N, 8*row_bytes) / V) lanes (as the layer's
-// forward); gains is [L-1][F].
+// Grid as the layer's forward; gains is [L-1][F].
 template <int IO, int SPK, int RESET, int V, int K, int L, bool OUT>
 __global__ __launch_bounds__(kBlock) void lif_stack_forward_kernel(LifK c, int64_t T, int64_t N, int64_t F,
                                                                    const void* __restrict__ x,
@@ -1018,17 +1045,29 @@ __global__ __launch_bounds__(kBlock) void lif_stack_forward_kernel(LifK c, int64
                                                                    int64_t row_bytes,
                                                                    float* __restrict__ saved,
                                                                    float* __restrict__ v_out) {
-    const int64_t first = xcd_contiguous_block() * kBlock * V;
-    const int64_t n0 = first + int64_t(threadIdx.x) * V;
-    const DenseIn<IO, V> in{x};
+    constexpr bool REST = has_rest<SPK, V>();
+    const int64_t whole = REST ? whole_vectors<SPK, V>(N) : N;
+    int64_t block = xcd_contiguous_block();
+    if constexpr (REST) {
+        if (whole < N) {
+            if (block == 0) {
+                const int64_t n0 = whole + threadIdx.x;
+                if (n0 >= N) return;
+                StackGains<1, L> G;
+                G.template init<IO>(gains, F, n0);
+                stack_forward_lanes<IO, SPK, RESET, 1, K, L, OUT>(c, DenseIn<IO, 1>{x}, G, T, N, n0, spikes, hidden,
+                                                                  row_bytes, saved, v_out);
+                return;
+            }
+            --block;
+        }
+    }
+    const int64_t n0 = (block * kBlock + threadIdx.x) * V;
+    if (n0 >= whole) return;
     StackGains<V, L> G;
-    G.template init<IO>(gains, F, n0, n0 < N);
-    if (first + kBlock * V <= N)
-        stack_forward_lanes<IO, SPK, RESET, V, K, L, OUT, true>(c, in, G, T, N, n0, spikes, hidden, row_bytes, saved,
-                                                                v_out);
-    else
-        stack_forward_lanes<IO, SPK, RESET, V, K, L, OUT, false>(c, in, G, T, N, n0, spikes, hidden, row_bytes,
-                                                                 saved, v_out);
+    G.template init<IO>(gains, F, n0);
+    stack_forward_lanes<IO, SPK, RESET, V, K, L, OUT>(c, DenseIn<IO, V>{x}, G, T, N, n0, spikes, hidden, row_bytes,
+                                                      saved, v_out);
 }
 
 // Backward of one chunk: recompute every layer's membranes from the state entering the
@@ -1140,7 +1179,7 @@ __global__ __launch_bounds__(kBlock) void lif_stack_backward_kernel(LifK c, int6
     const int64_t n0 = first + int64_t(threadIdx.x) * V;
     if (first + kBlock * V > N && n0 >= N) return;
     StackGains<V, L> G;
-    G.template init<IO>(gains, F, n0, true);
+    G.template init<IO>(gains, F, n0);
     stack_backward_lanes<IO, RESET, V, K, L>(c, DenseIn<IO, V>{x}, G, T, N, n0, saved, gs, gx);
 }
 

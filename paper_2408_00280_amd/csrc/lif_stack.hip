@@ -53,12 +53,12 @@ snn_status stack_forward_entry(int reset, int L, const StackPlan& p, const LifK&
     uint8_t* sp = static_cast<uint8_t*>(spikes);
     uint8_t* hd = static_cast<uint8_t*>(hidden);
     float* sv = static_cast<float*>(saved);
-    const dim3 g = grid_for(p.lanes);
     const bool out = hidden != nullptr || v_out != nullptr;
     auto go = [&](auto rst) {
         return stack_variant(p, L, [&](auto V, auto K, auto Lc) {
             constexpr int R = decltype(rst)::value;
             constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value, Lv = decltype(Lc)::value;
+            const dim3 g = wide_grid<SPK, Vc>(N);
             return out ? launch(lif_stack_forward_kernel<IO, SPK, R, Vc, Kc, Lv, true>, g, s, k, T, N, F, x, gains, sp,
                                 hd, p.row_bytes, sv, v_out)
                        : launch(lif_stack_forward_kernel<IO, SPK, R, Vc, Kc, Lv, false>, g, s, k, T, N, F, x, gains, sp,
