@@ -33,11 +33,6 @@ class LifConfig:
         return IO_DTYPES[self.io]
 
 
-def _require(ok: bool, what: str):
-    if not ok:
-        raise ValueError(what)
-
-
 def _TN(x: torch.Tensor):
     T = x.shape[0]
     return T, (x.numel() // T if T else 0)
@@ -46,12 +41,14 @@ def _TN(x: torch.Tensor):
 def alloc_forward(cfg: LifConfig, T: int, N: int, device, v_out: bool = False):
     """(spikes, saved uint8 bytes, v [T][N] float32 or None).  Spikes are [T][row_bytes]
     uint8 for "u8"/"bits" and [T][N] of the I/O dtype for "io"."""
-    c = cfg.c()
-    row = native.snn_spike_row_bytes(c, N)
+    return _alloc_forward(cfg, cfg.c(), T, N, device, v_out)
+
+
+def _alloc_forward(cfg: LifConfig, c: native.snn_lif_cfg, T: int, N: int, device, v_out: bool):
     if cfg.spk == "io":
         spikes = torch.empty((T, N), dtype=cfg.dtype, device=device)
     else:
-        spikes = torch.empty((T, row), dtype=torch.uint8, device=device)
+        spikes = torch.empty((T, native.snn_spike_row_bytes(c, N)), dtype=torch.uint8, device=device)
     saved = torch.empty(native.snn_lif_saved_bytes(c, T, N), dtype=torch.uint8, device=device)
     v = torch.empty((T, N), dtype=torch.float32, device=device) if v_out else None
     return spikes, saved, v
@@ -61,14 +58,16 @@ def forward(cfg: LifConfig, x: torch.Tensor, *, v_out: bool = False, out=None, v
             stream=None):
     """Fused forward of x[T, ...] (cfg.dtype, contiguous).  Returns (spikes, saved, v_or_None).
     v_in / v_last ([N] float32): segment state of a sequence split along time."""
-    _require(x.dtype == cfg.dtype and x.is_contiguous(), f"x must be a contiguous {cfg.dtype} tensor")
+    if x.dtype != cfg.dtype or not x.is_contiguous():
+        raise ValueError(f"x must be a contiguous {cfg.dtype} tensor")
     T, N = _TN(x)
-    spikes, saved, v = out if out is not None else alloc_forward(cfg, T, N, x.device, v_out)
+    c = cfg.c()
+    spikes, saved, v = out if out is not None else _alloc_forward(cfg, c, T, N, x.device, v_out)
     sv = saved if saved.numel() else None
     if v_in is None and v_last is None:
-        native.snn_lif_forward(cfg.c(), T, N, x, spikes, sv, v, stream)
+        native.snn_lif_forward(c, T, N, x, spikes, sv, v, stream)
     else:
-        native.snn_lif_forward_seg(cfg.c(), T, N, x, v_in, spikes, sv, v_last, v, stream)
+        native.snn_lif_forward_seg(c, T, N, x, v_in, spikes, sv, v_last, v, stream)
     return spikes, saved, v
 
 
@@ -76,8 +75,8 @@ def backward(cfg: LifConfig, x: torch.Tensor, saved: torch.Tensor, grad_s: torch
              grad_x: torch.Tensor | None = None, v_in=None, g_in=None, g_out=None, stream=None) -> torch.Tensor:
     """Fused backward; returns dL/dx with x's shape and dtype (in place if grad_x is grad_s).
     v_in / g_in / g_out ([N] float32): segment state of a sequence split along time."""
-    _require(grad_s.dtype == cfg.dtype and grad_s.shape == x.shape and grad_s.is_contiguous(),
-             f"grad_s must be a contiguous {cfg.dtype} tensor shaped like x")
+    if grad_s.dtype != cfg.dtype or grad_s.shape != x.shape or not grad_s.is_contiguous():
+        raise ValueError(f"grad_s must be a contiguous {cfg.dtype} tensor shaped like x")
     T, N = _TN(x)
     if grad_x is None:
         grad_x = torch.empty_like(grad_s)
@@ -92,15 +91,16 @@ def backward(cfg: LifConfig, x: torch.Tensor, saved: torch.Tensor, grad_s: torch
 def _check_gain_inputs(cfg: LifConfig, spikes_in: torch.Tensor, gain: torch.Tensor, T: int, B: int, F: int):
     N = B * F
     if cfg.spk == "io":
-        _require(spikes_in.dtype == cfg.dtype and tuple(spikes_in.shape) == (T, N),
-                 f"spikes_in must be a {cfg.dtype} tensor of shape ({T}, {N})")
+        if spikes_in.dtype != cfg.dtype or tuple(spikes_in.shape) != (T, N):
+            raise ValueError(f"spikes_in must be a {cfg.dtype} tensor of shape ({T}, {N})")
     else:
         row = native.snn_spike_row_bytes(cfg.c(), N)
-        _require(spikes_in.dtype == torch.uint8 and tuple(spikes_in.shape) == (T, row),
-                 f"spikes_in must be a uint8 tensor of shape ({T}, {row})")
-    _require(spikes_in.is_contiguous(), "spikes_in must be contiguous")
-    _require(gain.dtype == torch.float32 and gain.numel() == F and gain.is_contiguous(),
-             f"gain must be a contiguous float32 tensor of {F} values")
+        if spikes_in.dtype != torch.uint8 or tuple(spikes_in.shape) != (T, row):
+            raise ValueError(f"spikes_in must be a uint8 tensor of shape ({T}, {row})")
+    if not spikes_in.is_contiguous():
+        raise ValueError("spikes_in must be contiguous")
+    if gain.dtype != torch.float32 or gain.numel() != F or not gain.is_contiguous():
+        raise ValueError(f"gain must be a contiguous float32 tensor of {F} values")
 
 
 def forward_gain(cfg: LifConfig, spikes_in: torch.Tensor, gain: torch.Tensor, B: int, F: int, *,
@@ -123,8 +123,8 @@ def backward_gain(cfg: LifConfig, spikes_in: torch.Tensor, gain: torch.Tensor, s
     dtype (in place if grad_s_in is grad_s)."""
     T = spikes_in.shape[0]
     _check_gain_inputs(cfg, spikes_in, gain, T, B, F)
-    _require(grad_s.dtype == cfg.dtype and tuple(grad_s.shape) == (T, B * F) and grad_s.is_contiguous(),
-             f"grad_s must be a contiguous {cfg.dtype} tensor of shape ({T}, {B * F})")
+    if grad_s.dtype != cfg.dtype or tuple(grad_s.shape) != (T, B * F) or not grad_s.is_contiguous():
+        raise ValueError(f"grad_s must be a contiguous {cfg.dtype} tensor of shape ({T}, {B * F})")
     if grad_s_in is None:
         grad_s_in = torch.empty_like(grad_s)
     native.snn_lif_backward_gain(cfg.c(), T, B, F, spikes_in, gain, saved if saved.numel() else None, grad_s,
@@ -137,15 +137,16 @@ def stack_forward(cfg: LifConfig, x: torch.Tensor, gains: torch.Tensor, B: int, 
     """Forward of len(gains) + 1 layers fused across depth (gains: float32 [L-1, F]) on
     x[T, ...] (cfg.dtype, N = B*F per step).  Returns (spikes of the last layer, hidden
     spikes [L-1, T, ...] or None, saved, membranes [L, T, N] or None)."""
-    _require(x.dtype == cfg.dtype and x.is_contiguous(), f"x must be a contiguous {cfg.dtype} tensor")
-    _require(gains.dtype == torch.float32 and gains.dim() == 2 and gains.shape[1] == F and gains.is_contiguous(),
-             f"gains must be a contiguous float32 tensor of shape (L-1, {F})")
+    if x.dtype != cfg.dtype or not x.is_contiguous():
+        raise ValueError(f"x must be a contiguous {cfg.dtype} tensor")
+    if gains.dtype != torch.float32 or gains.dim() != 2 or gains.shape[1] != F or not gains.is_contiguous():
+        raise ValueError(f"gains must be a contiguous float32 tensor of shape (L-1, {F})")
     T, N = _TN(x)
-    _require(N == B * F, "x must hold B*F neurons per step")
+    if N != B * F:
+        raise ValueError("x must hold B*F neurons per step")
     L = gains.shape[0] + 1
     c = cfg.c()
-    row = native.snn_spike_row_bytes(c, N)
-    shape = (T, N) if cfg.spk == "io" else (T, row)
+    shape = (T, N) if cfg.spk == "io" else (T, native.snn_spike_row_bytes(c, N))
     sdt = cfg.dtype if cfg.spk == "io" else torch.uint8
     spikes = torch.empty(shape, dtype=sdt, device=x.device)
     hid = torch.empty((L - 1, *shape), dtype=sdt, device=x.device) if hidden else None
@@ -158,8 +159,8 @@ def stack_forward(cfg: LifConfig, x: torch.Tensor, gains: torch.Tensor, B: int, 
 def stack_backward(cfg: LifConfig, x: torch.Tensor, gains: torch.Tensor, saved: torch.Tensor, grad_s: torch.Tensor,
                    B: int, F: int, *, grad_x: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """Backward of stack_forward: dL/dx of layer 0 from dL/dy of the last layer."""
-    _require(grad_s.dtype == cfg.dtype and grad_s.shape == x.shape and grad_s.is_contiguous(),
-             f"grad_s must be a contiguous {cfg.dtype} tensor shaped like x")
+    if grad_s.dtype != cfg.dtype or grad_s.shape != x.shape or not grad_s.is_contiguous():
+        raise ValueError(f"grad_s must be a contiguous {cfg.dtype} tensor shaped like x")
     T, N = _TN(x)
     L = gains.shape[0] + 1
     if grad_x is None:

@@ -105,6 +105,10 @@ def _ptr(a):
 
 def _stream(s):
     if s is None:
+        # the handle torch.cuda.current_stream() wraps, without making the wrapper: 0.5 instead
+        # of 14 us per call in a training loop, whose backward runs on a thread of its own
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(s, torch.cuda.Stream):
         return s.cuda_stream
