@@ -25,11 +25,13 @@ int relay_lanes(const Plan& p, int64_t T) {
 #if !SNNLIF_GAIN
 
 template <int IO>
-snn_status backward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int64_t N, const void* x,
+snn_status backward_entry(int reset, const Plan& p, const LifK& k0, int64_t T, int64_t N, const void* x,
                           const void* saved, const void* gs, void* gx, const float* v_in, const float* g_in,
                           float* g_out, hipStream_t s) {
     const float* sv = static_cast<const float*>(saved);
     const BwdSeg seg{v_in, g_in, g_out};
+    LifK k = k0;
+    k.order = p.order;
     auto go = [&](auto rst) {
         if (p.narrow) {
             return narrow_variant(p, [&](auto K) {
@@ -51,9 +53,13 @@ snn_status backward_entry(int reset, const Plan& p, const LifK& k, int64_t T, in
                 return launch_blk(lif_backward_kernel<IO, R, Vc, Kc, false, B, false, true>, g, B, s, k, T, N, x, sv,
                                   gs, gx, seg);
             };
-            if (p.rb == 4) return ragged_variant<4>(p, T, N, ragged);
-            if (p.rb == 2) return ragged_variant<2>(p, T, N, ragged);
+            const bool sync_block = T > p.k && T >= kSyncBf16From && N / 2 >= 4 * kFillLanes;
+            if (p.rb == 4) return ragged_variant<4>(p, sync_block, ragged);
+            if (p.rb == 2) return ragged_variant<2>(p, sync_block, ragged);
         }
+        if (p.midsync)
+            return launch_blk(lif_backward_kernel<IO, decltype(rst)::value, 2, chunk_steps(2), false, kSyncBlock, true>,
+                              wide_grid<SNN_SPK_IO, 2>(N, kSyncBlock), kSyncBlock, s, k, T, N, x, sv, gs, gx, seg);
         return backward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
             constexpr int R = decltype(rst)::value;
             constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
@@ -86,11 +92,13 @@ template snn_status backward_entry<SNNLIF_IO>(int, const Plan&, const LifK&, int
 #endif
 
 template <int IO, int SPK>
-snn_status backward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t T, int64_t N, int64_t F,
+snn_status backward_gain_entry(int reset, const Plan& p, const LifK& k0, int64_t T, int64_t N, int64_t F,
                                const void* spikes_in, const float* gain, const void* saved, const void* gs,
                                void* gs_in, hipStream_t s) {
     const uint8_t* si = static_cast<const uint8_t*>(spikes_in);
     const float* sv = static_cast<const float*>(saved);
+    LifK k = k0;
+    k.order = p.order;
     auto go = [&](auto rst) {
         if (p.narrow) {
             return narrow_variant(p, [&](auto K) {

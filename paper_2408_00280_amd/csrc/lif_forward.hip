@@ -33,6 +33,16 @@ snn_status forward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int
                                           T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last);
             });
         }
+        if constexpr (IO == SNN_IO_F32) {
+            if (p.widef) {
+                constexpr int R = decltype(rst)::value, B = kSyncBlock, KC = chunk_steps(2);
+                const dim3 g = wide_grid<SPK, 4>(N, B);
+                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, 4, 4, KC, true, false, B>, g, B, s, k, T, N, x,
+                                          sp, p.row_bytes, sv, v_out, v_in, v_last)
+                             : launch_blk(lif_forward_kernel<IO, SPK, R, 4, 4, KC, false, false, B>, g, B, s, k, T, N,
+                                          x, sp, p.row_bytes, sv, v_out, v_in, v_last);
+            }
+        }
         if constexpr (IO == SNN_IO_BF16) {
             auto ragged = [&](auto V, auto K, auto blk) {
                 constexpr int R = decltype(rst)::value, B = decltype(blk)::value;
@@ -44,8 +54,9 @@ snn_status forward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int
                                           wide_grid<SPK, Vc>(N, B), B, s, k, T, N, x, sp, p.row_bytes, sv, v_out, v_in,
                                           v_last);
             };
-            if (p.rf == 8) return ragged_variant<8>(p, T, N, ragged);
-            if (p.rf == 2) return ragged_variant<2>(p, T, N, ragged);
+            const bool sync_block = T > p.k && N / 2 >= 4 * kFillLanes;
+            if (p.rf == 8) return ragged_variant<8>(p, sync_block, ragged);
+            if (p.rf == 2) return ragged_variant<2>(p, sync_block, ragged);
         }
         return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
             constexpr int R = decltype(rst)::value;
@@ -76,11 +87,13 @@ template snn_status forward_entry<SNNLIF_IO, SNNLIF_SPK>(int, const Plan&, const
 #else
 
 template <int IO, int SPK>
-snn_status forward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t T, int64_t N, int64_t F,
+snn_status forward_gain_entry(int reset, const Plan& p, const LifK& k0, int64_t T, int64_t N, int64_t F,
                               const void* spikes_in, const float* gain, void* spikes, void* saved, float* v_out,
                               hipStream_t s) {
     const uint8_t* si = static_cast<const uint8_t*>(spikes_in);
     uint8_t* sp = static_cast<uint8_t*>(spikes);
+    LifK k = k0;
+    k.order = p.order;
     float* sv = static_cast<float*>(saved);
     auto go = [&](auto rst) {
         if (p.narrow) {

@@ -68,6 +68,12 @@ __device__ __forceinline__ int64_t xcd_contiguous_block() {
     return int64_t(xcd) * q + (xcd < r ? xcd : r) + slot;
 }
 
+// Or in launch order, which keeps all the concurrent accesses of the chip to one row
+// together instead of those of each XCD (the plan chooses: in_launch_order).
+__device__ __forceinline__ int64_t block_of(const LifK& c) {
+    return c.order ? int64_t(blockIdx.x) : xcd_contiguous_block();
+}
+
 // ------------------------------------------------------------------------------------
 // Vectors of V consecutive neurons in the I/O dtype.
 template <int IO, int V>
@@ -526,12 +532,21 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
     if (v_last != nullptr) store_f32<V>(v_last + n0, v);
 }
 
+// Synced workgroups of kSyncBlock lanes run one to a CU: with two, which fewer registers
+// would allow, each CU walks two stretches of rows out of step (x[64][4194304] fp32 forward
+// 257 against 270 us, [100][3000000] 316 against 328 us).  7 waves per SIMD hold one such
+// workgroup of 16 waves, not two; the compiler reserves registers to that effect.
+constexpr int kMaxWaves = 8;   // per SIMD
+constexpr int waves_for(int blk) { return blk > kBlock ? 7 : kMaxWaves; }
+constexpr int min_waves_for(int blk) { return blk > kBlock ? 4 : 1; }
+
 // Grid: one lane per V neurons of whole_vectors, and a workgroup for the rest (wide_grid).
 // BLK: the workgroup size; above kBlock (layers of several chunks, not double-buffered)
 // the waves of a workgroup that lies wholly inside N meet at a barrier after every chunk.
 // RAGGED: N need not be a multiple of V.
 template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock, bool RAGGED = false>
-__global__ __launch_bounds__(BLK) void lif_forward_kernel(LifK c, int64_t T, int64_t N,
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(min_waves_for(BLK), waves_for(BLK))))
+void lif_forward_kernel(LifK c, int64_t T, int64_t N,
                                                           const void* __restrict__ x,
                                                           uint8_t* __restrict__ spikes,
                                                           int64_t row_bytes,
@@ -577,7 +592,7 @@ __global__ __launch_bounds__(BLK) void lif_forward_gain_kernel(LifK c, int64_t T
                                                                float* __restrict__ v_out) {
     constexpr bool REST = has_rest<SPK, V>();
     const int64_t whole = REST ? whole_vectors<SPK, V>(N) : N;
-    int64_t block = xcd_contiguous_block();
+    int64_t block = block_of(c);
     if constexpr (REST) {
         if (whole < N) {
             if (block == 0) {
@@ -775,7 +790,7 @@ __global__ __launch_bounds__(BLK) void lif_backward_kernel(LifK c, int64_t T, in
                                                            const void* gs, void* gx, BwdSeg seg) {
     static_assert(!SYNC || !PIPE, "barriers only in the single-buffered chunk loop");
     const int64_t whole = RAGGED ? whole_vectors<SNN_SPK_IO, V>(N) : N;
-    int64_t block = xcd_contiguous_block();
+    int64_t block = block_of(c);
     if constexpr (RAGGED) {
         if (whole < N) {
             if (block == 0) {
@@ -804,7 +819,7 @@ __global__ __launch_bounds__(kBlock) void lif_backward_gain_kernel(LifK c, int64
                                                                    int64_t row_bytes,
                                                                    const float* __restrict__ saved,
                                                                    const void* gs, void* gs_in) {
-    const int64_t first = xcd_contiguous_block() * kBlock * V;
+    const int64_t first = block_of(c) * kBlock * V;
     const int64_t n0 = first + int64_t(threadIdx.x) * V;
     if (first + kBlock * V > N && n0 >= N) return;
     GainSpikeIn<IO, SPK, V> in{spikes_in, row_bytes};
@@ -1047,7 +1062,7 @@ __global__ __launch_bounds__(kBlock) void lif_stack_forward_kernel(LifK c, int64
                                                                    float* __restrict__ v_out) {
     constexpr bool REST = has_rest<SPK, V>();
     const int64_t whole = REST ? whole_vectors<SPK, V>(N) : N;
-    int64_t block = xcd_contiguous_block();
+    int64_t block = block_of(c);
     if constexpr (REST) {
         if (whole < N) {
             if (block == 0) {
@@ -1175,7 +1190,7 @@ __global__ __launch_bounds__(kBlock) void lif_stack_backward_kernel(LifK c, int6
                                                                     const float* __restrict__ gains,
                                                                     const float* __restrict__ saved,
                                                                     const void* gs, void* gx) {
-    const int64_t first = xcd_contiguous_block() * kBlock * V;
+    const int64_t first = block_of(c) * kBlock * V;
     const int64_t n0 = first + int64_t(threadIdx.x) * V;
     if (first + kBlock * V > N && n0 >= N) return;
     StackGains<V, L> G;
