@@ -543,7 +543,8 @@ constexpr int min_waves_for(int blk) { return blk > kBlock ? 4 : 1; }
 // Grid: one lane per V neurons of whole_vectors, and a workgroup for the rest (wide_grid).
 // BLK: the workgroup size; above kBlock (layers of several chunks, not double-buffered)
 // the waves of a workgroup that lies wholly inside N meet at a barrier after every chunk.
-// RAGGED: N need not be a multiple of V.
+// RAGGED: N need not be a multiple of V, or of 64 with bit-packed spikes (the rest's code is
+// left out otherwise: merely present, it cost 1% of x[4][2^24]).
 template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock, bool RAGGED = false>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(min_waves_for(BLK), waves_for(BLK))))
 void lif_forward_kernel(LifK c, int64_t T, int64_t N,
@@ -555,10 +556,9 @@ void lif_forward_kernel(LifK c, int64_t T, int64_t N,
                                                           const float* __restrict__ v_in,
                                                           float* __restrict__ v_last) {
     static_assert(BLK <= kBlock || !PIPE, "barriers only in the single-buffered chunk loop");
-    constexpr bool REST = RAGGED || has_rest<SPK, V>();
-    const int64_t whole = REST ? whole_vectors<SPK, V>(N) : N;
+    const int64_t whole = RAGGED ? whole_vectors<SPK, V>(N) : N;
     int64_t block = xcd_contiguous_block();
-    if constexpr (REST) {
+    if constexpr (RAGGED) {
         if (whole < N) {
             if (block == 0) {
                 const int64_t n0 = whole + threadIdx.x;
