@@ -58,7 +58,7 @@ struct Plan {
     bool order;      // the backward's workgroups in launch order (in_launch_order)
     bool narrow;     // few neurons, several chunks: one neuron per lane in place of vf and vb,
                      // the forward in one-wave workgroups, the backward as a relay of waves
-    int64_t lanes;   // lanes in the forward grid
+    int64_t lanes;   // V-wide lanes that cover a row (the forward's vf)
     int64_t row_bytes;
 };
 
@@ -213,10 +213,11 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
 
 // The layer fed by the previous layer's spikes reads one spike word per lane and row (2-8
 // bytes) where the dense layer reads an I/O row of 8-16 bytes, so double-buffering its
-// chunks costs more in occupancy than it hides, but for the few lanes of a narrow layer (fp32 backward: 191 instead of 79 VGPRs, 2
-// instead of 6 waves per SIMD; forward 127 instead of 69).  Its chunks are single-buffered
-// at the dense layer's chunk length, so the checkpoint layout and snn_lif_saved_bytes stay
-// the dense layer's.  At N = 2^19 (event timing, three alternating rounds): fp32 u8 spikes,
+// chunks costs more in occupancy than it hides, but for the few lanes of a narrow layer
+// (fp32 backward: 191 instead of 79 VGPRs, 2 instead of 6 waves per SIMD; forward 127
+// instead of 69).  Its chunks are single-buffered at the dense layer's chunk length, so the
+// checkpoint layout and snn_lif_saved_bytes stay the dense layer's.  At N = 2^19 (event
+// timing, three alternating rounds): fp32 u8 spikes,
 // T = 32: forward 10.2 instead of 10.5 us, backward 29.7-29.9 instead of 30.7-31.0 us; bf16
 // bit spikes, T = 32: 11.1 instead of 11.8 us and 18.6 instead of 19.6-19.8 us; bf16 u8,
 // T = 64: backward 32.8 instead of 35.7-36.0 us, forward within 1%.
@@ -348,9 +349,6 @@ snn_status ragged_variant(const Plan& p, bool sync_block, F&& f) {
     return SNN_E_UNSUPPORTED;
 }
 
-// Calls f(V, K, PIPE) -- std::integral_constant / bool_constant tags -- with the lane width
-// and chunk length the plan chose for the forward (vf) or the backward (vb): the
-// combinations a kernel translation unit instantiates.
 // The chunk lengths of a narrow layer: those of the plans of 2 neurons (even N) and of 1.
 template <typename F>
 snn_status narrow_variant(const Plan& p, F&& f) {
@@ -361,6 +359,9 @@ snn_status narrow_variant(const Plan& p, F&& f) {
     return SNN_E_UNSUPPORTED;
 }
 
+// Calls f(V, K, PIPE) -- std::integral_constant / bool_constant tags -- with the lane width
+// and chunk length the plan chose for the forward (vf) or the backward (vb): the
+// combinations a kernel translation unit instantiates.
 template <int IO, int V, typename F>
 snn_status chunk_variant(const Plan& p, F&& f) {
     constexpr int K = chunk_steps(V == 8 ? 2 : V);   // a double-buffered 8-wide lane would pair with 2-wide
