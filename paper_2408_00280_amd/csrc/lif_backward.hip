@@ -25,13 +25,11 @@ int relay_lanes(const Plan& p, int64_t T) {
 #if !SNNLIF_GAIN
 
 template <int IO>
-snn_status backward_entry(int reset, const Plan& p, const LifK& k0, int64_t T, int64_t N, const void* x,
+snn_status backward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int64_t N, const void* x,
                           const void* saved, const void* gs, void* gx, const float* v_in, const float* g_in,
                           float* g_out, hipStream_t s) {
     const float* sv = static_cast<const float*>(saved);
     const BwdSeg seg{v_in, g_in, g_out};
-    LifK k = k0;
-    k.order = p.order;
     auto go = [&](auto rst) {
         if (p.narrow) {
             return narrow_variant(p, [&](auto K) {
@@ -92,13 +90,11 @@ template snn_status backward_entry<SNNLIF_IO>(int, const Plan&, const LifK&, int
 #endif
 
 template <int IO, int SPK>
-snn_status backward_gain_entry(int reset, const Plan& p, const LifK& k0, int64_t T, int64_t N, int64_t F,
+snn_status backward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t T, int64_t N, int64_t F,
                                const void* spikes_in, const float* gain, const void* saved, const void* gs,
                                void* gs_in, hipStream_t s) {
     const uint8_t* si = static_cast<const uint8_t*>(spikes_in);
     const float* sv = static_cast<const float*>(saved);
-    LifK k = k0;
-    k.order = p.order;
     auto go = [&](auto rst) {
         if (p.narrow) {
             return narrow_variant(p, [&](auto K) {

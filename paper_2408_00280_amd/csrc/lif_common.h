@@ -37,7 +37,6 @@ struct LifK {
     float alpha;  // surrogate sharpness
     float c_exp;  // -alpha * log2(e): e^{-alpha |u|} = 2^{c_exp |u|}
     float kth;    // k * V_th (soft-reset backward)
-    int order;    // workgroups take neurons in launch order (1) or one range per XCD (0)
 };
 
 }  // namespace snnlif

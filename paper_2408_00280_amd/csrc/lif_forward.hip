@@ -95,13 +95,11 @@ template snn_status forward_entry<SNNLIF_IO, SNNLIF_SPK>(int, const Plan&, const
 #else
 
 template <int IO, int SPK>
-snn_status forward_gain_entry(int reset, const Plan& p, const LifK& k0, int64_t T, int64_t N, int64_t F,
+snn_status forward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t T, int64_t N, int64_t F,
                               const void* spikes_in, const float* gain, void* spikes, void* saved, float* v_out,
                               hipStream_t s) {
     const uint8_t* si = static_cast<const uint8_t*>(spikes_in);
     uint8_t* sp = static_cast<uint8_t*>(spikes);
-    LifK k = k0;
-    k.order = p.order;
     float* sv = static_cast<float*>(saved);
     auto go = [&](auto rst) {
         if (p.narrow) {

@@ -55,7 +55,6 @@ struct Plan {
     int rb;          // lanes that take their place, all but a rest of N (else 0)
     bool widef;      // fp32 forward: 4 neurons per lane, 4-row batches, kSyncBlock workgroups
     bool midsync;    // the backward of a double-buffered plan single-buffered in synced workgroups
-    bool order;      // the backward's workgroups in launch order (in_launch_order)
     bool narrow;     // few neurons, several chunks: one neuron per lane in place of vf and vb,
                      // the forward in one-wave workgroups, the backward as a relay of waves
     int64_t lanes;   // V-wide lanes that cover a row (the forward's vf)
@@ -104,20 +103,6 @@ constexpr int kSyncBf16Chunks = 6;
 // -> 37.0 us, [200][98304] 44.6 -> 46.6 us: hence the limit.
 constexpr int64_t kNarrowN = 5 * int64_t(256) * 64;
 
-// Launch order keeps what the whole chip reads of one row at a time together; one range of
-// neurons per XCD keeps eight separate windows open in each of the 48-96 rows of a chunk.
-// From about a million neurons launch order is faster: fp32 backward at T = 16 and N = 1.5M
-// / 6M / 8.4M / 12.6M 52.7 -> 50.1 / 213.6 -> 205.8 / 276 -> 261 / 441 -> 400 us, bf16 N =
-// 3.2M / 14M 59.6 -> 54.0 / 262 -> 232 us, gain-fed backward x[32][2M] 101.6 -> 96.5 us; it
-// is slower on fewer (fp32 T = 8, N = 300K: 6.9 -> 7.8 us), and on rows a small multiple of
-// 4 MiB apart, where the rows of one column, then all in flight together, share their
-// memory channels: fp32 N = 2^20 / 2^21 / 2^22 37.0 -> 42.8 / 68.3 -> 87.4 / 130.9 -> 146.7
-// us, bf16 N = 2^22 70.1 -> 84.5 us (32 MiB apart, fp32 N = 2^23, it is faster again).
-inline bool in_launch_order(const snn_lif_cfg* c, int64_t N) {
-    const int64_t row = N * io_bytes(c), mib4 = int64_t(4) << 20;
-    return N > (int64_t(1) << 20) && !(row % mib4 == 0 && row <= 4 * mib4);
-}
-
 // How many 256ths of its rounds a layer fills in synced workgroups of kSyncBlock lanes with
 // v neurons each, one workgroup to a CU.
 inline int64_t sync_fill(int64_t N, int v) {
@@ -145,12 +130,8 @@ inline bool wide_sync_forward(const snn_lif_cfg* c, int64_t T, int64_t N) {
            (N * 4) % (int64_t(16) << 20) != 0;
 }
 
-// The bf16 backward of large layers of several 32-step chunks meets at barriers in
-// kSyncBlock workgroups from this many steps; shorter ones (a chunk and a tail) are faster
-// in 256-lane workgroups in launch order: T = 40, N = 3.2M / 5.2M / 16.8M 177 -> 144 / 265 ->
-// 227 / 731 -> 671 us, T = 48 216 -> 177 us.  At T = 64 the same is mixed (N = 2.2M / 4.5M
-// 173 -> 165 / 366 -> 382 us), while the barriers in launch order are never slower than in
-// XCD ranges: 173 -> 170 / 366 -> 358 us, N = 10.5M 836 -> 761 us.
+// The bf16 backward of large ragged layers (below) runs in kSyncBlock workgroups from this
+// many steps, a chunk and a tail in 256-lane ones.
 constexpr int64_t kSyncBf16From = 64;
 
 inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
@@ -176,7 +157,6 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     const bool long_walk = !p.pipe && T > p.k;   // several chunks, not double-buffered
     p.blkf = long_walk && p.vf >= 2 ? kSyncBlock : kBlock;   // the lane widths measured
     p.blkb = long_walk && p.vb == 2 ? kSyncBlock : kBlock;
-    if (c->io == SNN_IO_BF16 && p.k == 32 && T < kSyncBf16From && in_launch_order(c, N)) p.blkb = kBlock;
     p.syncb = c->io == SNN_IO_F32 || (T + p.k - 1) / p.k <= kSyncBf16Chunks;
     p.narrow = T > p.k && N <= kNarrowN;
     // bf16 rows are read 2 (large layers 8 and 4) neurons per lane whatever N is, a vector
@@ -194,17 +174,6 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     }
     p.midsync = !p.narrow && p.pipe && p.vb == 2 && sync_backward(c, N);
     p.widef = !p.narrow && p.k == chunk_steps(2) && wide_sync_forward(c, T, N);
-    // 32-step bf16 chunks: from 2M neurons (T = 32, N = 1.2M: 44.7 -> 51.7 us; 2.5M 99.0 ->
-    // 92.6 us), in synced workgroups not on rows 16 MiB apart (T = 64, N = 2^24: 1156 -> 1283
-    // us); not the 4-step chunk (bf16, N = 2^24: 65.5 -> 75.4 us); fp32 layers of several
-    // chunks are faster in XCD ranges (T = 32, N = 3M: 212.5 against 225 us)
-    p.order = p.k > 4 && in_launch_order(c, N);
-    if (p.k == 32) {
-        p.order = p.order && c->io == SNN_IO_BF16 && N >= 8 * kFillLanes && T <= kSyncBf16Chunks * 32 &&
-                  (T < kSyncBf16From || (N * io_bytes(c)) % (int64_t(16) << 20) != 0);
-    } else {
-        p.order = p.order && T <= p.k;
-    }
     p.row_bytes = spike_row_bytes(c, N);
     const int64_t covered = c->spk == SNN_SPK_BITS ? p.row_bytes * 8 : N;
     p.lanes = (covered + p.vf - 1) / p.vf;
@@ -224,7 +193,6 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
 inline Plan make_gain_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     Plan p = make_plan(c, T, N);
     p.pipe = false;
-    p.order = in_launch_order(c, N);
     return p;
 }
 
@@ -242,7 +210,6 @@ constexpr int64_t kStackNarrowN = 4 * kFillLanes;
 struct StackPlan {
     int v;
     int k;
-    bool order;      // workgroups in launch order
     int64_t lanes;
     int64_t row_bytes;
 };
@@ -251,7 +218,6 @@ inline StackPlan make_stack_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     StackPlan p;
     p.v = N % 2 != 0 || N <= kStackNarrowN ? 1 : 2;
     p.k = 16;
-    p.order = in_launch_order(c, N);
     for (int k : kShortChunks) {
         if (T <= k && k < p.k) {
             p.k = k;
@@ -282,7 +248,6 @@ inline LifK kernel_consts(const snn_lif_cfg* c) {
     k.alpha = c->alpha;
     k.c_exp = float(-double(c->alpha) * 1.4426950408889634074);  // -alpha log2(e)
     k.kth = c->decay * c->v_th;
-    k.order = 0;
     return k;
 }
 

@@ -60,18 +60,17 @@ __device__ __forceinline__ void st_bytes(uint8_t* p, E v) {   // an ordinary sto
 // Workgroups are dispatched round-robin over the 8 XCDs (workgroup b runs on XCD b % 8).
 // Renumber them so that each XCD walks one contiguous range of the neuron axis: with the
 // 32 MiB-apart rows of a [T][N] walk, this keeps each XCD's concurrent accesses local.
+// Launch order instead makes the backward of one chunk anything from 0.57 to 1.5 times as
+// fast, a ratio that belongs to the row's length and does not follow it in any simple way
+// (1,500 sizes of 4-64 MiB rows: 1.02 on average, 22% of them slower by 3% or more; fp32
+// x[16][8388608] 1.04, eight kilobytes either side 0.87-1.07, x[8][8388608] 0.92; gain-fed
+// layers 0.99 on average): not taken.
 constexpr unsigned kXcds = 8;
 
 __device__ __forceinline__ int64_t xcd_contiguous_block() {
     const unsigned nb = gridDim.x, b = blockIdx.x;
     const unsigned xcd = b % kXcds, slot = b / kXcds, q = nb / kXcds, r = nb % kXcds;
     return int64_t(xcd) * q + (xcd < r ? xcd : r) + slot;
-}
-
-// Or in launch order, which keeps all the concurrent accesses of the chip to one row
-// together instead of those of each XCD (the plan chooses: in_launch_order).
-__device__ __forceinline__ int64_t block_of(const LifK& c) {
-    return c.order ? int64_t(blockIdx.x) : xcd_contiguous_block();
 }
 
 // ------------------------------------------------------------------------------------
@@ -592,7 +591,7 @@ __global__ __launch_bounds__(BLK) void lif_forward_gain_kernel(LifK c, int64_t T
                                                                float* __restrict__ v_out) {
     constexpr bool REST = has_rest<SPK, V>();
     const int64_t whole = REST ? whole_vectors<SPK, V>(N) : N;
-    int64_t block = block_of(c);
+    int64_t block = xcd_contiguous_block();
     if constexpr (REST) {
         if (whole < N) {
             if (block == 0) {
@@ -790,7 +789,7 @@ __global__ __launch_bounds__(BLK) void lif_backward_kernel(LifK c, int64_t T, in
                                                            const void* gs, void* gx, BwdSeg seg) {
     static_assert(!SYNC || !PIPE, "barriers only in the single-buffered chunk loop");
     const int64_t whole = RAGGED ? whole_vectors<SNN_SPK_IO, V>(N) : N;
-    int64_t block = block_of(c);
+    int64_t block = xcd_contiguous_block();
     if constexpr (RAGGED) {
         if (whole < N) {
             if (block == 0) {
@@ -819,7 +818,7 @@ __global__ __launch_bounds__(kBlock) void lif_backward_gain_kernel(LifK c, int64
                                                                    int64_t row_bytes,
                                                                    const float* __restrict__ saved,
                                                                    const void* gs, void* gs_in) {
-    const int64_t first = block_of(c) * kBlock * V;
+    const int64_t first = xcd_contiguous_block() * kBlock * V;
     const int64_t n0 = first + int64_t(threadIdx.x) * V;
     if (first + kBlock * V > N && n0 >= N) return;
     GainSpikeIn<IO, SPK, V> in{spikes_in, row_bytes};
@@ -1062,7 +1061,7 @@ __global__ __launch_bounds__(kBlock) void lif_stack_forward_kernel(LifK c, int64
                                                                    float* __restrict__ v_out) {
     constexpr bool REST = has_rest<SPK, V>();
     const int64_t whole = REST ? whole_vectors<SPK, V>(N) : N;
-    int64_t block = block_of(c);
+    int64_t block = xcd_contiguous_block();
     if constexpr (REST) {
         if (whole < N) {
             if (block == 0) {
@@ -1190,7 +1189,7 @@ __global__ __launch_bounds__(kBlock) void lif_stack_backward_kernel(LifK c, int6
                                                                     const float* __restrict__ gains,
                                                                     const float* __restrict__ saved,
                                                                     const void* gs, void* gx) {
-    const int64_t first = block_of(c) * kBlock * V;
+    const int64_t first = xcd_contiguous_block() * kBlock * V;
     const int64_t n0 = first + int64_t(threadIdx.x) * V;
     if (first + kBlock * V > N && n0 >= N) return;
     StackGains<V, L> G;

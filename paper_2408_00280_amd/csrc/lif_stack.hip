@@ -47,15 +47,13 @@ snn_status stack_variant(const StackPlan& p, int L, F&& f) {
 #endif
 
 template <int IO, int SPK>
-snn_status stack_forward_entry(int reset, int L, const StackPlan& p, const LifK& k0, int64_t T, int64_t N, int64_t F,
+snn_status stack_forward_entry(int reset, int L, const StackPlan& p, const LifK& k, int64_t T, int64_t N, int64_t F,
                                const void* x, const float* gains, void* spikes, void* hidden, void* saved,
                                float* v_out, hipStream_t s) {
     uint8_t* sp = static_cast<uint8_t*>(spikes);
     uint8_t* hd = static_cast<uint8_t*>(hidden);
     float* sv = static_cast<float*>(saved);
     const bool out = hidden != nullptr || v_out != nullptr;
-    LifK k = k0;
-    k.order = p.order;
     auto go = [&](auto rst) {
         return stack_variant(p, L, [&](auto V, auto K, auto Lc) {
             constexpr int R = decltype(rst)::value;
@@ -77,12 +75,10 @@ template snn_status stack_forward_entry<SNNLIF_IO, SNNLIF_SPK>(int, int, const S
 #else
 
 template <int IO>
-snn_status stack_backward_entry(int reset, int L, const StackPlan& p, const LifK& k0, int64_t T, int64_t N, int64_t F,
+snn_status stack_backward_entry(int reset, int L, const StackPlan& p, const LifK& k, int64_t T, int64_t N, int64_t F,
                                 const void* x, const float* gains, const void* saved, const void* gs, void* gx,
                                 hipStream_t s) {
     const float* sv = static_cast<const float*>(saved);
-    LifK k = k0;
-    k.order = p.order;
     auto go = [&](auto rst) {
         return stack_variant(p, L, [&](auto V, auto K, auto Lc) {
             constexpr int R = decltype(rst)::value;
