@@ -111,13 +111,17 @@ inline int64_t sync_fill(int64_t N, int v) {
 }
 
 // A layer whose plan double-buffers runs its backward in such workgroups where they fill four
-// fifths of their rounds, on rows that are not a multiple of 2 MiB apart (2^19 fp32 neurons:
-// 38.9 -> 46.8 us): fp32 T = 40, N = 450K / 900K 45.5 -> 40.1 / 87.6 -> 77.9 us, T = 32, N =
-// 1.5M 112.7 -> 105.0 us, T = 256, N = 1M 589 -> 554 us, bf16 T = 96, N = 450K / 950K 63.4 ->
-// 55.4 / 142 -> 117 us; less filled, fp32 T = 32, N = 600K 42.5 -> 50.6 us, T = 96, N = 1.15M
-// (0.73) 272 -> 281 us.
-inline bool sync_backward(const snn_lif_cfg* c, int64_t N) {
-    return 5 * sync_fill(N, 2) >= 4 * 256 && (N * io_bytes(c)) % (int64_t(2) << 20) != 0;
+// fifths of their rounds: fp32 T = 40, N = 450K / 900K 45.5 -> 40.1 / 87.6 -> 77.9 us, T = 256,
+// N = 1M 589 -> 554 us, bf16 T = 96, N = 450K / 950K 63.4 -> 55.4 / 142 -> 117 us; less filled,
+// fp32 T = 96, N = 1.15M (0.73) 272 -> 281 us.  Not up to two full chunks (170 sizes of T = 17 to
+// 32: 1.01 times as fast on average and 0.79-1.16 each, [19][2096128] 109 -> 138 us); up to three
+// (T = 33 to 48: 1.07, 0.93-1.2) not within 2^14 neurons of a multiple of 2^19, whose fp32 rows
+// share memory channels ([44][2088960] bf16 0.93, [37][2096128] fp32 0.93); nor on rows exactly
+// a multiple of 2 MiB ([96][2^19] fp32 0.89).
+inline bool sync_backward(const snn_lif_cfg* c, int64_t T, int64_t N) {
+    const int64_t span = int64_t(1) << 19, off = N % span, near = off < span - off ? off : span - off;
+    return 5 * sync_fill(N, 2) >= 4 * 256 && (T > 48 || (T > 32 && near >= int64_t(1) << 14)) &&
+           (N * io_bytes(c)) % (int64_t(2) << 20) != 0;
 }
 
 // The fp32 forward of long layers takes 4 neurons per lane and 4 rows at a time in such
@@ -172,7 +176,7 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
         p.rf = wf > p.vf ? wf : 0;
         p.rb = wb > p.vb ? wb : 0;
     }
-    p.midsync = !p.narrow && p.pipe && p.vb == 2 && sync_backward(c, N);
+    p.midsync = !p.narrow && p.pipe && p.vb == 2 && sync_backward(c, T, N);
     p.widef = !p.narrow && p.k == chunk_steps(2) && wide_sync_forward(c, T, N);
     p.row_bytes = spike_row_bytes(c, N);
     const int64_t covered = c->spk == SNN_SPK_BITS ? p.row_bytes * 8 : N;

@@ -174,6 +174,24 @@ static void check_plans() {
                     }
 }
 
+// Sizes at which a plan lost against the general one: the rules keep them on the latter.
+static Plan plan_of(int io, int spk, int64_t T, int64_t N) {
+    const snn_lif_cfg c = cfg(0.5f, 1.0f, SNN_RESET_HARD, io, spk);
+    return make_plan(&c, T, N);
+}
+
+static void check_synced_backward_rule() {
+    // one full chunk and a tail, two full chunks
+    for (int64_t T : {17, 19, 22, 24, 28, 32})
+        for (int64_t N : {848294, 1375558, 1572862, 2096128}) CHECK(!plan_of(SNN_IO_F32, SNN_SPK_U8, T, N).midsync);
+    // two or three chunks next to a multiple of 2^19 neurons, on either side
+    for (int64_t N : {516096, 524290, 1564672, 2088960, 2096128})
+        for (int64_t T : {33, 44, 48}) CHECK(!plan_of(SNN_IO_BF16, SNN_SPK_U8, T, N).midsync);
+    // where it gains
+    for (int64_t N : {450000, 900000, 990000}) CHECK(plan_of(SNN_IO_F32, SNN_SPK_U8, 40, N).midsync);
+    for (int64_t N : {450000, 524284, 1000000, 2097146}) CHECK(plan_of(SNN_IO_BF16, SNN_SPK_U8, 96, N).midsync);
+}
+
 // ---------------------------------------------------------------- the oracle
 
 static uint64_t rng_state = 0x9E3779B97F4A7C15ull;
@@ -223,6 +241,7 @@ int main() {
     check_cfgs();
     check_shapes();
     check_plans();
+    check_synced_backward_rule();
     const int64_t shapes[][3] = {{0, 1, 1}, {1, 0, 3}, {1, 1, 1}, {2, 3, 5}, {17, 2, 33}, {40, 3, 7}, {5, 1, 1000}};
     for (const auto& s : shapes)
         for (int soft = 0; soft < 2; ++soft)
