@@ -125,12 +125,16 @@ inline bool sync_backward(const snn_lif_cfg* c, int64_t T, int64_t N) {
 }
 
 // The fp32 forward of long layers takes 4 neurons per lane and 4 rows at a time in such
-// workgroups where they fill 0.85 of their rounds: T = 200, N = 900K / 1M / 3M 190 -> 161 /
-// 214 -> 182 / 604 -> 574 us, T = 64, N = 1M / 3M / 6M 58.2 -> 57.0 / 207 -> 194 / 405 -> 390
-// us; less filled, T = 64, N = 1.5M / 2.2M (0.71 / 0.70) 91.5 -> 95.0 / 153 -> 160 us; on rows
-// 16 MiB apart T = 64, N = 2^22 260.6 -> 266.8 us; T = 32, N = 1.5M 45.0 -> 48.0 us.
+// workgroups where they fill 0.85 of their rounds, 0.9 of two rounds: T = 200, N = 900K / 1M /
+// 3M 190 -> 161 / 214 -> 182 / 604 -> 574 us, T = 64, N = 1M / 3M / 6M 58.2 -> 57.0 / 207 -> 194
+// / 405 -> 390 us; less filled, T = 64, N = 1.5M / 2.2M (0.71 / 0.70) 91.5 -> 95.0 / 153 -> 160
+// us; 0.85-0.9 of two rounds (69 sizes, rows of about 7 MiB) 1.00 times as fast on average and
+// 0.84-1.15 each (T = 128, N = 1835008 0.84, T = 80, N = 1859968 106 -> 116 us), while one round
+// and three to six gain 2-23% there.  Not on rows 16 MiB apart (T = 64, N = 2^22 260.6 -> 266.8
+// us) nor for fewer steps (T = 32, N = 1.5M 45.0 -> 48.0 us).
 inline bool wide_sync_forward(const snn_lif_cfg* c, int64_t T, int64_t N) {
-    return c->io == SNN_IO_F32 && T >= 64 && N % 4 == 0 && 100 * sync_fill(N, 4) >= 85 * 256 &&
+    const bool two_rounds = N > 4 * kSyncBlock * int64_t(256) && N <= 8 * kSyncBlock * int64_t(256);
+    return c->io == SNN_IO_F32 && T >= 64 && N % 4 == 0 && 100 * sync_fill(N, 4) >= (two_rounds ? 90 : 85) * 256 &&
            (N * 4) % (int64_t(16) << 20) != 0;
 }
 

@@ -192,6 +192,13 @@ static void check_synced_backward_rule() {
     for (int64_t N : {450000, 524284, 1000000, 2097146}) CHECK(plan_of(SNN_IO_BF16, SNN_SPK_U8, 96, N).midsync);
 }
 
+static void check_wide_forward_rule() {
+    for (int64_t N : {1785856, 1819112, 1835004, 1835008, 1859968})   // 0.85-0.9 of two rounds
+        for (int64_t T : {64, 128, 200}) CHECK(!plan_of(SNN_IO_F32, SNN_SPK_IO, T, N).widef);
+    for (int64_t N : {892476, 935124, 1000000, 1966080, 2097148, 2752512, 3000000})
+        CHECK(plan_of(SNN_IO_F32, SNN_SPK_IO, 128, N).widef);
+}
+
 // ---------------------------------------------------------------- the oracle
 
 static uint64_t rng_state = 0x9E3779B97F4A7C15ull;
@@ -242,6 +249,7 @@ int main() {
     check_shapes();
     check_plans();
     check_synced_backward_rule();
+    check_wide_forward_rule();
     const int64_t shapes[][3] = {{0, 1, 1}, {1, 0, 3}, {1, 1, 1}, {2, 3, 5}, {17, 2, 33}, {40, 3, 7}, {5, 1, 1000}};
     for (const auto& s : shapes)
         for (int soft = 0; soft < 2; ++soft)
