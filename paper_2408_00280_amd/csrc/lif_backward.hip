@@ -31,7 +31,7 @@ snn_status backward_entry(int reset, const Plan& p, const LifK& k, int64_t T, in
     const float* sv = static_cast<const float*>(saved);
     const BwdSeg seg{v_in, g_in, g_out};
     auto go = [&](auto rst) {
-        if (p.narrow) {
+        if (p.relay) {
             return narrow_variant(p, [&](auto K) {
                 constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
                 return launch_blk(lif_backward_relay_kernel<IO, R, Kc>, grid_for(N, kWave), relay_lanes(p, T), s, k, T,
@@ -96,7 +96,7 @@ snn_status backward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t 
     const uint8_t* si = static_cast<const uint8_t*>(spikes_in);
     const float* sv = static_cast<const float*>(saved);
     auto go = [&](auto rst) {
-        if (p.narrow) {
+        if (p.relay) {
             return narrow_variant(p, [&](auto K) {
                 constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
                 return launch_blk(lif_backward_gain_relay_kernel<IO, SPK, R, Kc>, grid_for(N, kWave), relay_lanes(p, T),

@@ -55,8 +55,9 @@ struct Plan {
     int rb;          // lanes that take their place, all but a rest of N (else 0)
     bool widef;      // fp32 forward: 4 neurons per lane, 4-row batches, kSyncBlock workgroups
     bool midsync;    // the backward of a double-buffered plan single-buffered in synced workgroups
-    bool narrow;     // few neurons, several chunks: one neuron per lane in place of vf and vb,
-                     // the forward in one-wave workgroups, the backward as a relay of waves
+    bool narrow;     // few neurons, several chunks: the forward with one neuron per lane in
+                     // place of vf, in one-wave workgroups
+    bool relay;      // and the backward as a relay of waves
     int64_t lanes;   // V-wide lanes that cover a row (the forward's vf)
     int64_t row_bytes;
 };
@@ -99,9 +100,25 @@ constexpr int kSyncBf16Chunks = 6;
 // many CUs as there are waves.  Its chunk length stays that of the wider plan.  Measured
 // against 2 neurons per lane in 256-lane workgroups, fp32 forward: x[1000][8192] 52.5 ->
 // 28.9 us, [200][16384] 14.2 -> 8.2 us, [200][65536] 19.0 -> 14.7 us, [200][80000] 20.1 ->
-// 17.3 us, [200][98304] 21.6 -> 20.9 us (bf16 17.2 -> 19.6 us); backward [200][80000] 41.3
-// -> 37.0 us, [200][98304] 44.6 -> 46.6 us: hence the limit.
+// 17.3 us, [200][98304] 21.6 -> 20.9 us (bf16 17.2 -> 19.6 us): hence the limit.
 constexpr int64_t kNarrowN = 5 * int64_t(256) * 64;
+
+// The relay keeps eight chunks of a workgroup's 64 neurons in flight, so with several
+// workgroups to a CU a long walk touches more rows at once than the plan of few waves and
+// two chunks: against that one (1,600 sizes) it is 1.1-5 times as fast on up to three waves of
+// neurons per CU, whatever T, and on all narrow layers of few steps (fp32 100, bf16 250), but
+// 0.75-1.0 beyond both (fp32 x[765][69148] 0.77, [176][80472] 0.91, bf16 [993][65778] 0.62,
+// [816][57246] 0.92).  Chunks of 32 steps (odd N) hold more registers: two and a half waves
+// per CU in fp32, three in bf16 (fp32 [932][42301] 0.91, [515][66958] 0.79, bf16 [256][64015]
+// 0.83), or less than two chunks (fp32 [64][49863] gain-fed 0.80); past 66 workgroups of 1,024
+// neurons it gains again (1.0-1.4; the plan it replaces then has two workgroups on some CUs).
+constexpr int64_t kWaveN = int64_t(256) * 64;   // neurons of one wave per CU
+
+inline bool relay_backward(const snn_lif_cfg* c, int64_t T, int64_t N, int k) {
+    const bool f32 = c->io == SNN_IO_F32;
+    if (k == chunk_steps(2)) return N <= 3 * kWaveN || T <= (f32 ? 100 : 250);
+    return N <= (f32 ? 5 * kWaveN / 2 : 3 * kWaveN) || T < 64 || N > 66 * 1024;
+}
 
 // How many 256ths of its rounds a layer fills in synced workgroups of kSyncBlock lanes with
 // v neurons each, one workgroup to a CU.
@@ -167,6 +184,7 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     p.blkb = long_walk && p.vb == 2 ? kSyncBlock : kBlock;
     p.syncb = c->io == SNN_IO_F32 || (T + p.k - 1) / p.k <= kSyncBf16Chunks;
     p.narrow = T > p.k && N <= kNarrowN;
+    p.relay = p.narrow && relay_backward(c, T, N, p.k);
     // bf16 rows are read 2 (large layers 8 and 4) neurons per lane whatever N is, a vector
     // needing only its elements' alignment; 2-byte loads, and chunks of 32 single neurons
     // whose tail waits at every row, cost far more than unaligned vectors: forward / backward

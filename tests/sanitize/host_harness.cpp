@@ -199,6 +199,31 @@ static void check_wide_forward_rule() {
         CHECK(plan_of(SNN_IO_F32, SNN_SPK_IO, 128, N).widef);
 }
 
+struct RelayCase {
+    int io;
+    int64_t T, N;
+    bool relay;
+};
+
+static void check_relay_rule() {
+    const RelayCase cases[] = {
+        // many steps of more than three waves per CU (two and a half: fp32, odd N)
+        {SNN_IO_F32, 765, 69148, false}, {SNN_IO_F32, 176, 80472, false}, {SNN_IO_F32, 983, 54130, false},
+        {SNN_IO_BF16, 993, 65778, false}, {SNN_IO_BF16, 890, 78730, false}, {SNN_IO_BF16, 816, 57246, false},
+        {SNN_IO_F32, 932, 42301, false}, {SNN_IO_F32, 515, 66958, false}, {SNN_IO_F32, 122, 64023, false},
+        {SNN_IO_F32, 64, 49863, false}, {SNN_IO_BF16, 256, 64015, false}, {SNN_IO_BF16, 165, 64357, false},
+        // where it gains: up to there, few steps, and odd N past two workgroups on some CUs
+        {SNN_IO_F32, 1000, 49152, true}, {SNN_IO_F32, 100, 81920, true}, {SNN_IO_BF16, 250, 81920, true},
+        {SNN_IO_F32, 1000, 40959, true}, {SNN_IO_F32, 63, 64001, true}, {SNN_IO_F32, 786, 81919, true},
+        {SNN_IO_BF16, 1000, 49151, true}, {SNN_IO_BF16, 400, 76001, true}, {SNN_IO_F32, 17, 2, true}};
+    for (const RelayCase& r : cases)
+        for (int spk : {SNN_SPK_U8, SNN_SPK_BITS, SNN_SPK_IO}) {
+            const snn_lif_cfg c = cfg(0.5f, 1.0f, SNN_RESET_HARD, r.io, spk);
+            CHECK(make_plan(&c, r.T, r.N).relay == r.relay);
+            CHECK(make_gain_plan(&c, r.T, r.N).relay == r.relay);
+        }
+}
+
 // ---------------------------------------------------------------- the oracle
 
 static uint64_t rng_state = 0x9E3779B97F4A7C15ull;
@@ -250,6 +275,7 @@ int main() {
     check_plans();
     check_synced_backward_rule();
     check_wide_forward_rule();
+    check_relay_rule();
     const int64_t shapes[][3] = {{0, 1, 1}, {1, 0, 3}, {1, 1, 1}, {2, 3, 5}, {17, 2, 33}, {40, 3, 7}, {5, 1, 1000}};
     for (const auto& s : shapes)
         for (int soft = 0; soft < 2; ++soft)
