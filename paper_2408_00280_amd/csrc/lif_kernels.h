@@ -542,6 +542,10 @@ constexpr int min_waves_for(int blk) { return blk > kBlock ? 4 : 1; }
 // Grid: one lane per V neurons of whole_vectors, and a workgroup for the rest (wide_grid).
 // BLK: the workgroup size; above kBlock (layers of several chunks, not double-buffered)
 // the waves of a workgroup that lies wholly inside N meet at a barrier after every chunk.
+// A workgroup wholly inside N runs a copy of the code without any lane's exit: with one copy
+// under the per-lane exit the double-buffered bf16 backward of 55-110K neurons ran 2.5% slower
+// (90 sizes; x[158][101010] 26.7 -> 27.5 us) and x[4][2^24] 0.7%; a uniform test in front of the
+// exit changed nothing.  Ragged forwards have one copy (two cost bit spikes 1%).
 // RAGGED: N need not be a multiple of V, or of 64 with bit-packed spikes (the rest's code is
 // left out otherwise: merely present, it cost 1% of x[4][2^24]).
 template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock, bool RAGGED = false>
@@ -571,7 +575,7 @@ void lif_forward_kernel(LifK c, int64_t T, int64_t N,
     }
     const int64_t first = block * BLK * V, n0 = first + int64_t(threadIdx.x) * V;
     const DenseIn<IO, V> in{x};
-    if (BLK > kBlock && first + BLK * V <= whole)
+    if ((BLK > kBlock || !RAGGED) && first + BLK * V <= whole)
         forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, DenseIn<IO, V>, (BLK > kBlock)>(
             c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
     else if (n0 < whole)
@@ -803,7 +807,7 @@ __global__ __launch_bounds__(BLK) void lif_backward_kernel(LifK c, int64_t T, in
     }
     const int64_t first = block * BLK * V, n0 = first + int64_t(threadIdx.x) * V;
     const DenseIn<IO, V> in{x};
-    if (SYNC && first + BLK * V <= whole)
+    if ((SYNC || !RAGGED) && first + BLK * V <= whole)
         backward_lanes<IO, RESET, V, K, PIPE, false, DenseIn<IO, V>, SYNC>(c, in, T, N, n0, saved, gs, gx, seg);
     else if (n0 < whole)
         backward_lanes<IO, RESET, V, K, PIPE, false>(c, in, T, N, n0, saved, gs, gx, seg);
