@@ -191,12 +191,18 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     // of x[20][1010625] 25.3 -> 20.8 / 96.8 -> 30.0 us, [40][300001] 22.0 -> 15.0 / 66.7 -> 21.0
     // us, [17][3897755] (bit spikes) 50.2 -> 28.1 / 314 -> 88.6 us, [64][4000002] (bit spikes,
     // 8 instead of 2 per lane forward) 139 -> 112 us.  fp32 rows of odd N keep one neuron, a
-    // dword, per lane.
+    // dword, per lane.  So do few bf16 neurons, which leave lanes idle: narrow layers, and of
+    // one-chunk layers as small the forward (350 sizes of 2-32 steps: two per lane 0.81-1.2
+    // times as fast, 0.95 on average; [15][1587] 4.4 -> 5.2 us; up to 8 steps also to 2^17
+    // neurons, 0.97 on average of 30 sizes, [7][90825] 3.2 -> 3.5 us) and the backward of a whole
+    // chunk ([32][4929] 4.7 -> 6.1 us) or of less than four waves; the backward of a partial
+    // chunk gains there too ([20][1201] 12.1 -> 9.7 us).
     p.rf = p.rb = 0;
-    if (c->io == SNN_IO_BF16 && !p.narrow) {
+    if (c->io == SNN_IO_BF16) {
         const int wf = N / 8 >= kFillLanes ? 8 : 2, wb = T <= 16 && N / 4 >= kFillLanes ? 4 : 2;
-        p.rf = wf > p.vf ? wf : 0;
-        p.rb = wb > p.vb ? wb : 0;
+        const bool few = N <= kNarrowN;
+        p.rf = N > (T <= 8 ? int64_t(1) << 17 : kNarrowN) && wf > p.vf ? wf : 0;
+        p.rb = (!few || (T < p.k && N >= 4 * kWave)) && wb > p.vb ? wb : 0;
     }
     p.midsync = !p.narrow && p.pipe && p.vb == 2 && sync_backward(c, T, N);
     p.widef = !p.narrow && p.k == chunk_steps(2) && wide_sync_forward(c, T, N);

@@ -199,6 +199,22 @@ static void check_wide_forward_rule() {
         CHECK(plan_of(SNN_IO_F32, SNN_SPK_IO, 128, N).widef);
 }
 
+static void check_ragged_rule() {
+    for (int spk : {SNN_SPK_U8, SNN_SPK_BITS, SNN_SPK_IO}) {
+        for (int64_t T : {2, 3, 15, 16, 20, 31, 32})        // few neurons: one per lane forward
+            for (int64_t N : {69, 1587, 5463, 65281, 81919}) CHECK(plan_of(SNN_IO_BF16, spk, T, N).rf == 0);
+        for (int64_t T : {4, 8, 16, 32})                    // and in the backward of a whole chunk
+            for (int64_t N : {75, 741, 4929, 61155}) CHECK(plan_of(SNN_IO_BF16, spk, T, N).rb == 0);
+        for (int64_t T : {2, 15, 20}) CHECK(plan_of(SNN_IO_BF16, spk, T, 145).rb == 0);
+        for (int64_t T : {3, 15, 20, 31}) CHECK(plan_of(SNN_IO_BF16, spk, T, 1201).rb == 2);
+        for (int64_t T : {2, 5, 8}) CHECK(plan_of(SNN_IO_BF16, spk, T, 131071).rf == 0);
+        for (int64_t T : {9, 20, 33, 400}) {
+            const Plan p = plan_of(SNN_IO_BF16, spk, T, 81921);
+            CHECK(p.rf == 2 && p.rb == 2);
+        }
+    }
+}
+
 struct RelayCase {
     int io;
     int64_t T, N;
@@ -276,6 +292,7 @@ int main() {
     check_synced_backward_rule();
     check_wide_forward_rule();
     check_relay_rule();
+    check_ragged_rule();
     const int64_t shapes[][3] = {{0, 1, 1}, {1, 0, 3}, {1, 1, 1}, {2, 3, 5}, {17, 2, 33}, {40, 3, 7}, {5, 1, 1000}};
     for (const auto& s : shapes)
         for (int soft = 0; soft < 2; ++soft)
