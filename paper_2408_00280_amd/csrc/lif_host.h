@@ -57,7 +57,7 @@ struct Plan {
     bool midsync;    // the backward of a double-buffered plan single-buffered in synced workgroups
     bool narrow;     // few neurons, several chunks: the forward with one neuron per lane in
                      // place of vf, in one-wave workgroups
-    bool relay;      // and the backward as a relay of waves
+    bool relay;      // the same: the backward as a relay of waves
     int64_t lanes;   // V-wide lanes that cover a row (the forward's vf)
     int64_t row_bytes;
 };
@@ -103,6 +103,26 @@ constexpr int kSyncBf16Chunks = 6;
 // 17.3 us, [200][98304] 21.6 -> 20.9 us (bf16 17.2 -> 19.6 us): hence the limit.
 constexpr int64_t kNarrowN = 5 * int64_t(256) * 64;
 
+constexpr int64_t kWaveN = int64_t(256) * 64;   // neurons of one wave per CU
+
+// The narrow forward does not pay for all of them either.  Against the plan it replaces (2,900
+// sizes, most 1.1-1.8 times as fast): bf16 bit spikes of even N, whose words one lane per wave
+// stores, 0.83-1.0 beyond one wave of neurons per CU up to 64 steps, beyond three up to 128
+// (x[44][77454] 0.83); fp32 spikes in the I/O dtype, many steps beyond three and a half waves
+// per CU 0.86-1.0 ([389][76402] 0.86, odd [706][62503] 0.88; odd N past 66 workgroups of 1,024
+// neurons 1.2-1.4).  Gain-fed layers, which it double-buffers and the other plan does not: bf16
+// spikes in the I/O dtype as the bit spikes ([47][74240] 0.70), and odd N of up to two 32-step
+// chunks ([48][53805] 0.76).
+inline bool narrow_forward(const snn_lif_cfg* c, int64_t T, int64_t N, int k, bool gain) {
+    const bool f32 = c->io == SNN_IO_F32, odd = k == chunk_steps(1);
+    if (gain && odd && T <= 2 * k) return false;
+    if (!f32 && !odd && c->spk == (gain ? SNN_SPK_IO : SNN_SPK_BITS))
+        return N <= kWaveN || T > (N <= 3 * kWaveN ? 64 : 128);
+    if (f32 && c->spk == SNN_SPK_IO && T > 8 * k && (odd || !gain))
+        return N <= 7 * kWaveN / 2 || (odd && N > 66 * 1024);
+    return true;
+}
+
 // The relay keeps eight chunks of a workgroup's 64 neurons in flight, so with several
 // workgroups to a CU a long walk touches more rows at once than the plan of few waves and
 // two chunks: against that one (1,600 sizes) it is 1.1-5 times as fast on up to three waves of
@@ -112,8 +132,6 @@ constexpr int64_t kNarrowN = 5 * int64_t(256) * 64;
 // per CU in fp32, three in bf16 (fp32 [932][42301] 0.91, [515][66958] 0.79, bf16 [256][64015]
 // 0.83), or less than two chunks (fp32 [64][49863] gain-fed 0.80); past 66 workgroups of 1,024
 // neurons it gains again (1.0-1.4; the plan it replaces then has two workgroups on some CUs).
-constexpr int64_t kWaveN = int64_t(256) * 64;   // neurons of one wave per CU
-
 inline bool relay_backward(const snn_lif_cfg* c, int64_t T, int64_t N, int k) {
     const bool f32 = c->io == SNN_IO_F32;
     if (k == chunk_steps(2)) return N <= 3 * kWaveN || T <= (f32 ? 100 : 250);
@@ -183,8 +201,9 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     p.blkf = long_walk && p.vf >= 2 ? kSyncBlock : kBlock;   // the lane widths measured
     p.blkb = long_walk && p.vb == 2 ? kSyncBlock : kBlock;
     p.syncb = c->io == SNN_IO_F32 || (T + p.k - 1) / p.k <= kSyncBf16Chunks;
-    p.narrow = T > p.k && N <= kNarrowN;
-    p.relay = p.narrow && relay_backward(c, T, N, p.k);
+    const bool small = T > p.k && N <= kNarrowN;
+    p.narrow = small && narrow_forward(c, T, N, p.k, false);
+    p.relay = small && relay_backward(c, T, N, p.k);
     // bf16 rows are read 2 (large layers 8 and 4) neurons per lane whatever N is, a vector
     // needing only its elements' alignment; 2-byte loads, and chunks of 32 single neurons
     // whose tail waits at every row, cost far more than unaligned vectors: forward / backward
@@ -204,8 +223,8 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
         p.rf = N > (T <= 8 ? int64_t(1) << 17 : kNarrowN) && wf > p.vf ? wf : 0;
         p.rb = (!few || (T < p.k && N >= 4 * kWave)) && wb > p.vb ? wb : 0;
     }
-    p.midsync = !p.narrow && p.pipe && p.vb == 2 && sync_backward(c, T, N);
-    p.widef = !p.narrow && p.k == chunk_steps(2) && wide_sync_forward(c, T, N);
+    p.midsync = p.pipe && p.vb == 2 && sync_backward(c, T, N);
+    p.widef = p.k == chunk_steps(2) && wide_sync_forward(c, T, N);
     p.row_bytes = spike_row_bytes(c, N);
     const int64_t covered = c->spk == SNN_SPK_BITS ? p.row_bytes * 8 : N;
     p.lanes = (covered + p.vf - 1) / p.vf;
@@ -225,6 +244,7 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
 inline Plan make_gain_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     Plan p = make_plan(c, T, N);
     p.pipe = false;
+    p.narrow = T > p.k && N <= kNarrowN && narrow_forward(c, T, N, p.k, true);
     return p;
 }
 

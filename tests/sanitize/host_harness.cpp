@@ -215,6 +215,30 @@ static void check_ragged_rule() {
     }
 }
 
+struct NarrowCase {
+    int io, spk;
+    int64_t T, N;
+    bool dense, gain;
+};
+
+static void check_narrow_forward_rule() {
+    const NarrowCase cases[] = {
+        {SNN_IO_BF16, SNN_SPK_BITS, 44, 77454, false, true},  {SNN_IO_BF16, SNN_SPK_BITS, 26, 57140, false, true},
+        {SNN_IO_BF16, SNN_SPK_BITS, 128, 49154, false, true}, {SNN_IO_BF16, SNN_SPK_BITS, 129, 49154, true, true},
+        {SNN_IO_BF16, SNN_SPK_BITS, 64, 49152, false, true},  {SNN_IO_BF16, SNN_SPK_BITS, 65, 49152, true, true},
+        {SNN_IO_BF16, SNN_SPK_BITS, 17, 16384, true, true},   {SNN_IO_BF16, SNN_SPK_IO, 47, 74240, true, false},
+        {SNN_IO_BF16, SNN_SPK_IO, 26, 33820, true, false},    {SNN_IO_BF16, SNN_SPK_IO, 200, 74240, true, true},
+        {SNN_IO_F32, SNN_SPK_IO, 389, 76402, false, true},    {SNN_IO_F32, SNN_SPK_IO, 128, 76402, true, true},
+        {SNN_IO_F32, SNN_SPK_IO, 706, 62503, false, false},   {SNN_IO_F32, SNN_SPK_IO, 786, 81919, true, true},
+        {SNN_IO_F32, SNN_SPK_U8, 48, 53805, true, false},     {SNN_IO_F32, SNN_SPK_U8, 65, 53805, true, true},
+        {SNN_IO_F32, SNN_SPK_U8, 1000, 8192, true, true},     {SNN_IO_BF16, SNN_SPK_U8, 1000, 81920, true, true}};
+    for (const NarrowCase& r : cases) {
+        const snn_lif_cfg c = cfg(0.5f, 1.0f, SNN_RESET_HARD, r.io, r.spk);
+        CHECK(make_plan(&c, r.T, r.N).narrow == r.dense);
+        CHECK(make_gain_plan(&c, r.T, r.N).narrow == r.gain);
+    }
+}
+
 struct RelayCase {
     int io;
     int64_t T, N;
@@ -291,6 +315,7 @@ int main() {
     check_plans();
     check_synced_backward_rule();
     check_wide_forward_rule();
+    check_narrow_forward_rule();
     check_relay_rule();
     check_ragged_rule();
     const int64_t shapes[][3] = {{0, 1, 1}, {1, 0, 3}, {1, 1, 1}, {2, 3, 5}, {17, 2, 33}, {40, 3, 7}, {5, 1, 1000}};
