@@ -36,12 +36,11 @@ snn_status forward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int
         if constexpr (IO == SNN_IO_F32) {
             if (p.widef) {
                 constexpr int R = decltype(rst)::value, B = kSyncBlock, KC = chunk_steps(2);
-                constexpr bool Q = has_rest<SPK, 4>();
-                const dim3 g = wide_grid<SPK, 4>(N, B);
-                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, 4, 4, KC, true, false, B, Q>, g, B, s, k, T, N,
-                                          x, sp, p.row_bytes, sv, v_out, v_in, v_last)
-                             : launch_blk(lif_forward_kernel<IO, SPK, R, 4, 4, KC, false, false, B, Q>, g, B, s, k, T,
-                                          N, x, sp, p.row_bytes, sv, v_out, v_in, v_last);
+                const dim3 g = covered_grid<SPK, 4>(N, B);
+                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, 4, 4, KC, true, false, B>, g, B, s, k, T, N, x,
+                                          sp, p.row_bytes, sv, v_out, v_in, v_last)
+                             : launch_blk(lif_forward_kernel<IO, SPK, R, 4, 4, KC, false, false, B>, g, B, s, k, T, N,
+                                          x, sp, p.row_bytes, sv, v_out, v_in, v_last);
             }
         }
         if constexpr (IO == SNN_IO_BF16) {
@@ -66,18 +65,11 @@ snn_status forward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int
             constexpr int FB = forward_batch(IO, Vc, Kc, Pc);
             auto run = [&](auto blk) {
                 constexpr int B = decltype(blk)::value;
-                const dim3 g = wide_grid<SPK, Vc>(N, B);
-                auto go_rest = [&](auto rest) {
-                    constexpr bool Q = decltype(rest)::value;
-                    return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, true, Pc, B, Q>, g, B, s, k,
-                                              T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last)
-                                 : launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, false, Pc, B, Q>, g, B, s, k,
-                                              T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last);
-                };
-                if constexpr (has_rest<SPK, Vc>()) {
-                    if (N % kWave) return go_rest(std::true_type{});
-                }
-                return go_rest(std::false_type{});
+                const dim3 g = covered_grid<SPK, Vc>(N, B);
+                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, true, Pc, B>, g, B, s, k, T, N, x,
+                                          sp, p.row_bytes, sv, v_out, v_in, v_last)
+                             : launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, false, Pc, B>, g, B, s, k, T, N, x,
+                                          sp, p.row_bytes, sv, v_out, v_in, v_last);
             };
             if constexpr (!Pc && Vc >= 2) {
                 if (p.blkf == kSyncBlock) return run(IntC<kSyncBlock>{});

@@ -312,6 +312,14 @@ dim3 wide_grid(int64_t N, int blk = kBlock) {
     return dim3(unsigned((whole / V + blk - 1) / blk + (whole < N)));
 }
 
+// V-wide lanes over N, a multiple of V, and over the whole words of bit-packed spikes: lanes
+// beyond N only complete their word.
+template <int SPK, int V>
+dim3 covered_grid(int64_t N, int blk = kBlock) {
+    const int64_t covered = SPK == SNN_SPK_BITS ? (N + kWave - 1) / kWave * kWave : N;
+    return dim3(unsigned((covered / V + blk - 1) / blk));
+}
+
 template <typename Tuple, size_t... I>
 void fill_argv(Tuple& t, void** argv, std::index_sequence<I...>) {
     ((argv[I] = static_cast<void*>(&std::get<I>(t))), ...);

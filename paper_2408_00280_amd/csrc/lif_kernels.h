@@ -353,9 +353,9 @@ __device__ __forceinline__ void load_f32(const float* p, float (&f)[V]) {
 // On gfx9-family GPUs one in-order counter (vmcnt) covers every outstanding vector load
 // AND store, and the compiler's wait before a use is only as precise as the control flow
 // allows: a load or store under a branch makes the merged count conservative, and then a
-// wait for an old row also waits for younger loads.  So: no load or store of a lane is
-// guarded (whole_vectors), checkpoint loads are issued before the row loads they precede in
-// use, and double-buffered loops peel their first iteration so that the loop body issues
+// wait for an old row also waits for younger loads.  So: lanes are guarded only in a partial
+// workgroup that completes words of bit-packed spikes, checkpoint loads are issued before the
+// row loads they precede in use, and double-buffered loops peel their first iteration so that the loop body issues
 // every load unconditionally.
 //
 // Where the input current comes from is a policy:
@@ -424,7 +424,8 @@ __device__ __forceinline__ void load_rows(const In& in, typename In::raw (&buf)[
 
 template <int IO, int SPK, int RESET, int V, int K, bool VOUT, bool FULL, typename In>
 __device__ __forceinline__ void forward_rows(const LifK& c, const In& in, const typename In::raw (&xr)[K], int64_t N,
-                                             int64_t t0, int kn, int64_t n0, uint8_t* __restrict__ spikes,
+                                             int64_t t0, int kn, int64_t n0, bool active,
+                                             uint8_t* __restrict__ spikes,
                                              int64_t row_bytes, float* __restrict__ v_out, float (&v)[V],
                                              bool (&y)[V]) {
 #pragma unroll
@@ -432,8 +433,8 @@ __device__ __forceinline__ void forward_rows(const LifK& c, const In& in, const 
         if (FULL || i < kn) {
 #pragma unroll
             for (int j = 0; j < V; ++j) lif_step<RESET>(c, v[j], y[j], in.get(xr[i], j, n0));
-            SpikeOut<IO, SPK, V>::store(spikes, row_bytes, t0 + i, n0, true, y);
-            if (VOUT) store_f32<V>(v_out + (t0 + i) * N + n0, v);
+            SpikeOut<IO, SPK, V>::store(spikes, row_bytes, t0 + i, n0, active, y);
+            if (VOUT && active) store_f32<V>(v_out + (t0 + i) * N + n0, v);
         }
     }
 }
@@ -447,12 +448,16 @@ __device__ __forceinline__ void forward_rows(const LifK& c, const In& in, const 
 // Segment state (a sequence split along time): v_in, if not null, is the membrane the
 // previous segment ended with, and the spike state entering the first step is v_in >= V_th;
 // v_last, if not null, receives the membrane after the last step.
-template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, typename In, bool SYNC = false>
+// ALL: every lane's neurons lie inside N; else lanes beyond it load and store nothing and
+// report no spikes: they complete the last word of bit-packed spikes.
+template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, typename In, bool SYNC = false,
+          bool ALL = true>
 __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64_t T, int64_t N, int64_t n0,
                                               uint8_t* __restrict__ spikes, int64_t row_bytes,
                                               float* __restrict__ saved, float* __restrict__ v_out,
                                               const float* __restrict__ v_in, float* __restrict__ v_last) {
     using raw = typename In::raw;
+    const bool active = ALL || n0 < N;
     float v[V];
     bool y[V];
 #pragma unroll
@@ -460,7 +465,7 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
         v[j] = c.rest;  // v^0 = V_rest
         y[j] = false;   // no spike before the first step
     }
-    if (v_in != nullptr) {
+    if (v_in != nullptr && active) {
         load_f32<V>(v_in + n0, v);
 #pragma unroll
         for (int j = 0; j < V; ++j) y[j] = v[j] >= c.th;
@@ -473,18 +478,19 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
     // and back-edge and make the compiler's waits conservative.
     auto load = [&](raw (&buf)[K], int64_t ch) {
         __builtin_amdgcn_sched_barrier(0);
-        load_rows<In, K, true, false>(in, buf, N, ch * K, K, n0);
+        if (active) load_rows<In, K, true, false>(in, buf, N, ch * K, K, n0);
         __builtin_amdgcn_sched_barrier(0);
     };
     static_assert(KC % K == 0 && (!PIPE || KC == K), "checkpoint interval");
     // ckpt: true_type = this chunk is never the last (checkpoint unconditionally)
     auto step = [&](const raw (&buf)[K], int64_t ch, auto ckpt) {
-        forward_rows<IO, SPK, RESET, V, K, VOUT, true>(c, in, buf, N, ch * K, K, n0, spikes, row_bytes, v_out, v, y);
+        forward_rows<IO, SPK, RESET, V, K, VOUT, true>(c, in, buf, N, ch * K, K, n0, active, spikes, row_bytes, v_out,
+                                                       v, y);
         if constexpr (KC == K) {
-            if (decltype(ckpt)::value || ch < last) store_f32<V>(saved + ch * N + n0, v);
+            if ((decltype(ckpt)::value || ch < last) && active) store_f32<V>(saved + ch * N + n0, v);
         } else {
             const int64_t t_end = (ch + 1) * K;
-            if (t_end % KC == 0 && t_end < T) store_f32<V>(saved + (t_end / KC - 1) * N + n0, v);
+            if (t_end % KC == 0 && t_end < T && active) store_f32<V>(saved + (t_end / KC - 1) * N + n0, v);
         }
     };
     constexpr std::true_type not_last{};
@@ -524,11 +530,11 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
         }
     }
     if (k_tail) {
-        load_rows<In, K, false, false>(in, a, N, n_full * K, k_tail, n0);
-        forward_rows<IO, SPK, RESET, V, K, VOUT, false>(c, in, a, N, n_full * K, k_tail, n0, spikes, row_bytes, v_out,
-                                                        v, y);
+        if (active) load_rows<In, K, false, false>(in, a, N, n_full * K, k_tail, n0);
+        forward_rows<IO, SPK, RESET, V, K, VOUT, false>(c, in, a, N, n_full * K, k_tail, n0, active, spikes, row_bytes,
+                                                        v_out, v, y);
     }
-    if (v_last != nullptr) store_f32<V>(v_last + n0, v);
+    if (v_last != nullptr && active) store_f32<V>(v_last + n0, v);
 }
 
 // Synced workgroups of kSyncBlock lanes run one to a CU: with two, which fewer registers
@@ -539,15 +545,16 @@ constexpr int kMaxWaves = 8;   // per SIMD
 constexpr int waves_for(int blk) { return blk > kBlock ? 7 : kMaxWaves; }
 constexpr int min_waves_for(int blk) { return blk > kBlock ? 4 : 1; }
 
-// Grid: one lane per V neurons of whole_vectors, and a workgroup for the rest (wide_grid).
+// Grid: one lane per V neurons, over whole words of bit-packed spikes (covered_grid), the
+// last workgroup's lanes guarded; RAGGED (N no multiple of V): over whole_vectors, and a
+// workgroup of one neuron per lane for the rest (wide_grid).  That workgroup in place of the
+// guards cost bit spikes of N % 64 != 0 1-10% (x[20][57838] bf16 4.9 -> 5.4 us).
 // BLK: the workgroup size; above kBlock (layers of several chunks, not double-buffered)
 // the waves of a workgroup that lies wholly inside N meet at a barrier after every chunk.
 // A workgroup wholly inside N runs a copy of the code without any lane's exit: with one copy
 // under the per-lane exit the double-buffered bf16 backward of 55-110K neurons ran 2.5% slower
 // (90 sizes; x[158][101010] 26.7 -> 27.5 us) and x[4][2^24] 0.7%; a uniform test in front of the
-// exit changed nothing.  Ragged forwards have one copy (two cost bit spikes 1%).
-// RAGGED: N need not be a multiple of V, or of 64 with bit-packed spikes (the rest's code is
-// left out otherwise: merely present, it cost 1% of x[4][2^24]).
+// exit changed nothing.  Ragged forwards have one copy.
 template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock, bool RAGGED = false>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(min_waves_for(BLK), waves_for(BLK))))
 void lif_forward_kernel(LifK c, int64_t T, int64_t N,
@@ -577,6 +584,9 @@ void lif_forward_kernel(LifK c, int64_t T, int64_t N,
     const DenseIn<IO, V> in{x};
     if ((BLK > kBlock || !RAGGED) && first + BLK * V <= whole)
         forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, DenseIn<IO, V>, (BLK > kBlock)>(
+            c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
+    else if (!RAGGED && SPK == SNN_SPK_BITS && V > 1)
+        forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, DenseIn<IO, V>, false, false>(
             c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
     else if (n0 < whole)
         forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE>(c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in,
