@@ -23,58 +23,15 @@ snn_status forward_entry(int reset, const Plan& p, const LifK& k, int64_t T, int
     uint8_t* sp = static_cast<uint8_t*>(spikes);
     float* sv = static_cast<float*>(saved);
     auto go = [&](auto rst) {
-        if (p.narrow) {
-            return narrow_variant(p, [&](auto K) {
-                constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
-                const dim3 g = grid_for(N, kWave);
-                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, 1, Kc, Kc, true, true, kWave>, g, kWave, s, k,
-                                          T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last)
-                             : launch_blk(lif_forward_kernel<IO, SPK, R, 1, Kc, Kc, false, true, kWave>, g, kWave, s, k,
-                                          T, N, x, sp, p.row_bytes, sv, v_out, v_in, v_last);
-            });
-        }
-        if constexpr (IO == SNN_IO_F32) {
-            if (p.widef) {
-                constexpr int R = decltype(rst)::value, B = kSyncBlock, KC = chunk_steps(2);
-                const dim3 g = covered_grid<SPK, 4>(N, B);
-                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, 4, 4, KC, true, false, B>, g, B, s, k, T, N, x,
-                                          sp, p.row_bytes, sv, v_out, v_in, v_last)
-                             : launch_blk(lif_forward_kernel<IO, SPK, R, 4, 4, KC, false, false, B>, g, B, s, k, T, N,
-                                          x, sp, p.row_bytes, sv, v_out, v_in, v_last);
-            }
-        }
-        if constexpr (IO == SNN_IO_BF16) {
-            auto ragged = [&](auto V, auto K, auto blk) {
-                constexpr int R = decltype(rst)::value, B = decltype(blk)::value;
-                constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value, FB = forward_batch(IO, Vc, Kc, false);
-                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, true, false, B, true>,
-                                          wide_grid<SPK, Vc>(N, B), B, s, k, T, N, x, sp, p.row_bytes, sv, v_out, v_in,
-                                          v_last)
-                             : launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, false, false, B, true>,
-                                          wide_grid<SPK, Vc>(N, B), B, s, k, T, N, x, sp, p.row_bytes, sv, v_out, v_in,
-                                          v_last);
-            };
-            const bool sync_block = T > p.k && N / 2 >= 4 * kFillLanes;
-            if (p.rf == 8) return ragged_variant<8>(p, sync_block, ragged);
-            if (p.rf == 2) return ragged_variant<2>(p, sync_block, ragged);
-        }
-        return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
-            constexpr int R = decltype(rst)::value;
-            constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
-            constexpr bool Pc = decltype(PIPE)::value;
-            constexpr int FB = forward_batch(IO, Vc, Kc, Pc);
-            auto run = [&](auto blk) {
-                constexpr int B = decltype(blk)::value;
-                const dim3 g = covered_grid<SPK, Vc>(N, B);
-                return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, true, Pc, B>, g, B, s, k, T, N, x,
-                                          sp, p.row_bytes, sv, v_out, v_in, v_last)
-                             : launch_blk(lif_forward_kernel<IO, SPK, R, Vc, FB, Kc, false, Pc, B>, g, B, s, k, T, N, x,
-                                          sp, p.row_bytes, sv, v_out, v_in, v_last);
-            };
-            if constexpr (!Pc && Vc >= 2) {
-                if (p.blkf == kSyncBlock) return run(IntC<kSyncBlock>{});
-            }
-            return run(IntC<kBlock>{});
+        return forward_route<IO>(p, T, N, [&](auto V, auto FB, auto K, auto PIPE, auto blk, auto ragged) {
+            constexpr int R = decltype(rst)::value, Vc = decltype(V)::value, Fc = decltype(FB)::value;
+            constexpr int Kc = decltype(K)::value, B = decltype(blk)::value;
+            constexpr bool Pc = decltype(PIPE)::value, Q = decltype(ragged)::value;
+            const dim3 g = forward_grid<SPK, Vc, Q>(N, B);
+            return v_out ? launch_blk(lif_forward_kernel<IO, SPK, R, Vc, Fc, Kc, true, Pc, B, Q>, g, B, s, k, T, N, x,
+                                      sp, p.row_bytes, sv, v_out, v_in, v_last)
+                         : launch_blk(lif_forward_kernel<IO, SPK, R, Vc, Fc, Kc, false, Pc, B, Q>, g, B, s, k, T, N, x,
+                                      sp, p.row_bytes, sv, v_out, v_in, v_last);
         });
     };
     return reset == SNN_RESET_SOFT ? go(IntC<SNN_RESET_SOFT>{}) : go(IntC<SNN_RESET_HARD>{});
@@ -94,29 +51,15 @@ snn_status forward_gain_entry(int reset, const Plan& p, const LifK& k, int64_t T
     uint8_t* sp = static_cast<uint8_t*>(spikes);
     float* sv = static_cast<float*>(saved);
     auto go = [&](auto rst) {
-        if (p.narrow) {
-            return narrow_variant(p, [&](auto K) {
-                constexpr int R = decltype(rst)::value, Kc = decltype(K)::value;
-                const dim3 gn = grid_for(N, kWave);
-                return v_out ? launch_blk(lif_forward_gain_kernel<IO, SPK, R, 1, Kc, Kc, true, true, kWave>, gn, kWave,
-                                          s, k, T, N, F, si, gain, sp, p.row_bytes, sv, v_out)
-                             : launch_blk(lif_forward_gain_kernel<IO, SPK, R, 1, Kc, Kc, false, true, kWave>, gn, kWave,
-                                          s, k, T, N, F, si, gain, sp, p.row_bytes, sv, v_out);
-            });
-        }
-        return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
-            constexpr int R = decltype(rst)::value;
-            constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
-            if constexpr (decltype(PIPE)::value) {
-                return SNN_E_UNSUPPORTED;   // the gain-fed layer's plan never double-buffers
-            } else {
-                constexpr int FB = forward_batch(IO, Vc, Kc, false);
-                const dim3 g = wide_grid<SPK, Vc>(N);
-                return v_out ? launch(lif_forward_gain_kernel<IO, SPK, R, Vc, FB, Kc, true>, g, s, k, T, N, F, si,
-                                      gain, sp, p.row_bytes, sv, v_out)
-                             : launch(lif_forward_gain_kernel<IO, SPK, R, Vc, FB, Kc, false>, g, s, k, T, N, F,
-                                      si, gain, sp, p.row_bytes, sv, v_out);
-            }
+        return forward_gain_route<IO>(p, [&](auto V, auto FB, auto K, auto PIPE, auto blk) {
+            constexpr int R = decltype(rst)::value, Vc = decltype(V)::value, Fc = decltype(FB)::value;
+            constexpr int Kc = decltype(K)::value, B = decltype(blk)::value;
+            constexpr bool Pc = decltype(PIPE)::value;
+            const dim3 g = wide_grid<SPK, Vc>(N, B);
+            return v_out ? launch_blk(lif_forward_gain_kernel<IO, SPK, R, Vc, Fc, Kc, true, Pc, B>, g, B, s, k, T, N, F,
+                                      si, gain, sp, p.row_bytes, sv, v_out)
+                         : launch_blk(lif_forward_gain_kernel<IO, SPK, R, Vc, Fc, Kc, false, Pc, B>, g, B, s, k, T, N,
+                                      F, si, gain, sp, p.row_bytes, sv, v_out);
         });
     };
     return reset == SNN_RESET_SOFT ? go(IntC<SNN_RESET_SOFT>{}) : go(IntC<SNN_RESET_HARD>{});

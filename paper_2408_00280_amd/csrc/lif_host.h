@@ -58,7 +58,6 @@ struct Plan {
     bool narrow;     // few neurons, several chunks: the forward with one neuron per lane in
                      // place of vf, in one-wave workgroups
     bool relay;      // the same: the backward as a relay of waves
-    int64_t lanes;   // V-wide lanes that cover a row (the forward's vf)
     int64_t row_bytes;
 };
 
@@ -226,8 +225,6 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     p.midsync = p.pipe && p.vb == 2 && sync_backward(c, T, N);
     p.widef = p.k == chunk_steps(2) && wide_sync_forward(c, T, N);
     p.row_bytes = spike_row_bytes(c, N);
-    const int64_t covered = c->spk == SNN_SPK_BITS ? p.row_bytes * 8 : N;
-    p.lanes = (covered + p.vf - 1) / p.vf;
     return p;
 }
 
@@ -262,7 +259,6 @@ constexpr int64_t kStackNarrowN = 4 * kFillLanes;
 struct StackPlan {
     int v;
     int k;
-    int64_t lanes;
     int64_t row_bytes;
 };
 
@@ -277,8 +273,6 @@ inline StackPlan make_stack_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
         }
     }
     p.row_bytes = spike_row_bytes(c, N);
-    const int64_t covered = c->spk == SNN_SPK_BITS ? p.row_bytes * 8 : N;
-    p.lanes = (covered + p.v - 1) / p.v;
     return p;
 }
 
@@ -310,14 +304,6 @@ template <int SPK, int V>
 dim3 wide_grid(int64_t N, int blk = kBlock) {
     const int64_t whole = whole_vectors<SPK, V>(N);
     return dim3(unsigned((whole / V + blk - 1) / blk + (whole < N)));
-}
-
-// V-wide lanes over N, a multiple of V, and over the whole words of bit-packed spikes: lanes
-// beyond N only complete their word.
-template <int SPK, int V>
-dim3 covered_grid(int64_t N, int blk = kBlock) {
-    const int64_t covered = SPK == SNN_SPK_BITS ? (N + kWave - 1) / kWave * kWave : N;
-    return dim3(unsigned((covered / V + blk - 1) / blk));
 }
 
 template <typename Tuple, size_t... I>
@@ -353,22 +339,22 @@ constexpr int forward_batch(int io, int v, int k, bool pipe) {
 }
 
 // Ragged layers (bf16): V neurons per lane, single-buffered chunks of the plan's length, in
-// kSyncBlock workgroups where layers of their size take them.
-template <int V, int K, typename F>
+// kSyncBlock workgroups (SYNC) where layers of their size take them.
+template <int V, int K, bool SYNC, typename F>
 snn_status ragged_blocks(bool sync_block, F&& f) {
-    if constexpr (K == 32) {
+    if constexpr (K == 32 && SYNC) {
         if (sync_block) return f(IntC<V>{}, IntC<K>{}, IntC<kSyncBlock>{});
     }
     return f(IntC<V>{}, IntC<K>{}, IntC<kBlock>{});
 }
 
-template <int V, typename F>
+template <int V, bool SYNC, typename F>
 snn_status ragged_variant(const Plan& p, bool sync_block, F&& f) {
     switch (p.k) {
-        case 4: return ragged_blocks<V, 4>(sync_block, f);
-        case 8: return ragged_blocks<V, 8>(sync_block, f);
-        case 16: return ragged_blocks<V, 16>(sync_block, f);
-        case 32: if constexpr (V != 4) return ragged_blocks<V, 32>(sync_block, f);
+        case 4: return ragged_blocks<V, 4, SYNC>(sync_block, f);
+        case 8: return ragged_blocks<V, 8, SYNC>(sync_block, f);
+        case 16: return ragged_blocks<V, 16, SYNC>(sync_block, f);
+        case 32: if constexpr (V != 4) return ragged_blocks<V, 32, SYNC>(sync_block, f);
                  break;
     }
     return SNN_E_UNSUPPORTED;
@@ -389,10 +375,12 @@ snn_status narrow_variant(const Plan& p, F&& f) {
 // combinations a kernel translation unit instantiates.
 template <int IO, int V, typename F>
 snn_status chunk_variant(const Plan& p, F&& f) {
-    constexpr int K = chunk_steps(V == 8 ? 2 : V);   // a double-buffered 8-wide lane would pair with 2-wide
-    if (p.pipe) {
-        if (p.k != K) return SNN_E_UNSUPPORTED;   // no plan pairs another chunk with these lanes
-        return f(IntC<V>{}, IntC<K>{}, std::true_type{});
+    if (p.pipe) {   // few lanes: none wider than 2
+        if constexpr (V <= 2) {
+            constexpr int K = chunk_steps(V);
+            if (p.k == K) return f(IntC<V>{}, IntC<K>{}, std::true_type{});
+        }
+        return SNN_E_UNSUPPORTED;   // no plan pairs another chunk with these lanes
     }
     switch (p.k) {   // the long chunks, and the single-chunk layers of kShortChunks
         case 4: return f(IntC<V>{}, IntC<4>{}, std::false_type{});
@@ -424,6 +412,112 @@ snn_status backward_variant(const Plan& p, F&& f) {
         case 1: return chunk_variant<IO, 1>(p, f);
     }
     return SNN_E_UNSUPPORTED;
+}
+
+// The kernels of a plan: each of the following calls its functor with the tags of the one
+// kernel that the plan launches, and is the only place where the plan's switches are weighed
+// against each other.
+//
+// The dense forward: f(V, FB, K, PIPE, BLK, RAGGED) -- neurons per lane, rows per load batch,
+// steps per chunk, double-buffered, workgroup size, N no multiple of V.
+template <int IO, typename F>
+snn_status forward_route(const Plan& p, int64_t T, int64_t N, F&& f) {
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr int kLong = IO == SNN_IO_F32 ? chunk_steps(2) : 32;   // the chunk of layers not double-buffered
+    if (p.narrow) return narrow_variant(p, [&](auto K) { return f(IntC<1>{}, K, K, yes, IntC<kWave>{}, no); });
+    if constexpr (IO == SNN_IO_F32) {
+        if (p.widef) return f(IntC<4>{}, IntC<4>{}, IntC<chunk_steps(2)>{}, no, IntC<kSyncBlock>{}, no);
+    } else {
+        auto ragged = [&](auto V, auto K, auto blk) {
+            constexpr int FB = forward_batch(IO, decltype(V)::value, decltype(K)::value, false);
+            return f(V, IntC<FB>{}, K, no, blk, yes);
+        };
+        const bool sync_block = T > p.k && N / 2 >= 4 * kFillLanes;
+        if (p.rf == 8) return ragged_variant<8, true>(p, sync_block, ragged);
+        if (p.rf == 2) return ragged_variant<2, false>(p, false, ragged);   // fewer than fill the chip
+    }
+    return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) -> snn_status {
+        constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
+        constexpr bool Pc = decltype(PIPE)::value;
+        // bf16 layers of odd N and several chunks are narrow or ragged; 32-step chunks of even
+        // N take 8 neurons per lane
+        if constexpr (IO == SNN_IO_BF16 && ((Vc == 1 && Pc) || (Vc == 2 && Kc == 32))) {
+            return SNN_E_UNSUPPORTED;
+        } else {
+            constexpr IntC<forward_batch(IO, Vc, Kc, Pc)> FB{};
+            if constexpr (!Pc && Vc >= 2 && Kc == kLong) {
+                if (p.blkf == kSyncBlock) return f(V, FB, K, PIPE, IntC<kSyncBlock>{}, no);
+            }
+            return f(V, FB, K, PIPE, IntC<kBlock>{}, no);
+        }
+    });
+}
+
+// The dense backward: f(V, K, PIPE, BLK, SYNC, RAGGED), SYNC for the barriers, or relay(K).
+template <int IO, typename F, typename G>
+snn_status backward_route(const Plan& p, int64_t T, int64_t N, F&& f, G&& relay) {
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr int kLong = IO == SNN_IO_F32 ? chunk_steps(2) : 32;
+    if (p.relay) return narrow_variant(p, relay);
+    if constexpr (IO == SNN_IO_BF16) {
+        auto ragged = [&](auto V, auto K, auto blk) {
+            if constexpr (decltype(blk)::value == kSyncBlock) {
+                if (p.syncb) return f(V, K, no, blk, yes, yes);
+            }
+            return f(V, K, no, blk, no, yes);
+        };
+        const bool sync_block = T > p.k && T >= kSyncBf16From && N / 2 >= 4 * kFillLanes;
+        if (p.rb == 4) return ragged_variant<4, false>(p, false, ragged);   // one chunk
+        if (p.rb == 2) return ragged_variant<2, true>(p, sync_block, ragged);
+    }
+    if (p.midsync) return f(IntC<2>{}, IntC<chunk_steps(2)>{}, no, IntC<kSyncBlock>{}, yes, no);
+    return backward_variant<IO>(p, [&](auto V, auto K, auto PIPE) {
+        if constexpr (!decltype(PIPE)::value && decltype(V)::value == 2 && decltype(K)::value == kLong) {
+            if (p.blkb == kSyncBlock) {
+                if constexpr (IO == SNN_IO_BF16) {
+                    if (!p.syncb) return f(V, K, PIPE, IntC<kSyncBlock>{}, no, no);
+                }
+                return f(V, K, PIPE, IntC<kSyncBlock>{}, yes, no);
+            }
+        }
+        return f(V, K, PIPE, IntC<kBlock>{}, no, no);
+    });
+}
+
+// The gain-fed layer, single-buffered but for the narrow forward: f(V, FB, K, PIPE, BLK), and
+// f(V, K) or relay(K).
+template <int IO, typename F>
+snn_status forward_gain_route(const Plan& p, F&& f) {
+    if (p.narrow)
+        return narrow_variant(p, [&](auto K) { return f(IntC<1>{}, K, K, std::true_type{}, IntC<kWave>{}); });
+    return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) -> snn_status {
+        if constexpr (decltype(PIPE)::value) {
+            return SNN_E_UNSUPPORTED;
+        } else {
+            constexpr IntC<forward_batch(IO, decltype(V)::value, decltype(K)::value, false)> FB{};
+            return f(V, FB, K, PIPE, IntC<kBlock>{});
+        }
+    });
+}
+
+template <int IO, typename F, typename G>
+snn_status backward_gain_route(const Plan& p, F&& f, G&& relay) {
+    if (p.relay) return narrow_variant(p, relay);
+    return backward_variant<IO>(p, [&](auto V, auto K, auto PIPE) -> snn_status {
+        if constexpr (decltype(PIPE)::value) return SNN_E_UNSUPPORTED;
+        else return f(V, K);
+    });
+}
+
+// The dense forward's grid.  A workgroup's neurons are whole words of bit-packed spikes, so
+// the lanes that complete the last word are in the last workgroup.
+template <int SPK, int V, bool RAGGED>
+dim3 forward_grid(int64_t N, int blk) {
+    static_assert(kBlock % kWave == 0 && kSyncBlock % kWave == 0);
+    if constexpr (RAGGED) return wide_grid<SPK, V>(N, blk);
+    else return grid_for((N + V - 1) / V, blk);
 }
 
 // v_in / v_last / g_in / g_out: the segment state of a sequence split along time (each may

@@ -545,8 +545,8 @@ constexpr int kMaxWaves = 8;   // per SIMD
 constexpr int waves_for(int blk) { return blk > kBlock ? 7 : kMaxWaves; }
 constexpr int min_waves_for(int blk) { return blk > kBlock ? 4 : 1; }
 
-// Grid: one lane per V neurons, over whole words of bit-packed spikes (covered_grid), the
-// last workgroup's lanes guarded; RAGGED (N no multiple of V): over whole_vectors, and a
+// Grid (forward_grid): one lane per V neurons, the last workgroup's lanes guarded where they
+// complete a word of bit-packed spikes; RAGGED (N no multiple of V): over whole_vectors, and a
 // workgroup of one neuron per lane for the rest (wide_grid).  That workgroup in place of the
 // guards cost bit spikes of N % 64 != 0 1-10% (x[20][57838] bf16 4.9 -> 5.4 us).
 // BLK: the workgroup size; above kBlock (layers of several chunks, not double-buffered)

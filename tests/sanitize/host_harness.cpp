@@ -98,80 +98,189 @@ static void check_shapes() {
     CHECK(check_shape(2, std::numeric_limits<int64_t>::max()) == SNN_E_SHAPE);
 }
 
-// The instantiated variants are the ones forward_variant / backward_variant dispatch to.
-struct Probe {
-    template <typename V, typename K, typename P>
-    snn_status operator()(V, K, P) const {
+// What is launched: the functors below take the place of the launchers and check the one
+// kernel and grid that each route picks.
+
+// The lanes of grid x blk workgroups, v neurons each, cover `end` and no workgroup more.
+static void check_grid(dim3 grid, int blk, int v, int64_t end) {
+    CHECK(grid.y == 1 && grid.z == 1);
+    CHECK(int64_t(grid.x) * blk * v >= end);
+    CHECK((int64_t(grid.x) - 1) * blk * v < end);
+}
+
+// wide_grid: whole vectors (whole spike words), and one workgroup for a rest smaller than it.
+template <int SPK, int V>
+static void check_wide_grid(dim3 grid, int blk, int64_t N) {
+    const int64_t whole = whole_vectors<SPK, V>(N), rest = N - whole;
+    CHECK(whole >= 0 && rest >= 0 && rest < blk && whole % V == 0);
+    if (SPK == SNN_SPK_BITS && V > 1) CHECK(whole % kWave == 0);
+    if (rest == 0) return check_grid(grid, blk, V, whole);
+    CHECK(whole % V == 0 && grid.x >= 1);
+    if (whole == 0) CHECK(grid.x == 1);
+    else check_grid(dim3(grid.x - 1), blk, V, whole);
+}
+
+template <int SPK>
+struct ForwardProbe {
+    const Plan& p;
+    int64_t T, N;
+    template <typename V, typename FB, typename K, typename P, typename B, typename Q>
+    snn_status operator()(V, FB, K, P, B, Q) const {
+        constexpr int v = V::value, blk = B::value;
+        CHECK(K::value == p.k && p.k % FB::value == 0);           // checkpoints after whole batches
+        if (P::value) CHECK(FB::value == K::value && T > p.k);
+        if (blk > kBlock) CHECK(!P::value && T > p.k);            // barriers: several chunks
+        const dim3 g = forward_grid<SPK, v, Q::value>(N, blk);
+        if (Q::value) {
+            check_wide_grid<SPK, v>(g, blk, N);
+        } else {
+            CHECK(N % v == 0);                                    // lanes never straddle the row end
+            check_grid(g, blk, v, SPK == SNN_SPK_BITS ? p.row_bytes * 8 : N);   // every spike word written
+        }
         return SNN_OK;
     }
 };
+
+struct BackwardProbe {
+    const Plan& p;
+    int64_t T, N;
+    template <typename V, typename K, typename P, typename B, typename S, typename Q>
+    snn_status operator()(V, K, P, B, S, Q) const {
+        constexpr int v = V::value, blk = B::value;
+        CHECK(K::value == p.k);                                   // reads the forward's checkpoints
+        if (P::value) CHECK(T > p.k);
+        if (S::value) CHECK(blk > kBlock && !P::value && T > p.k);
+        if (!Q::value) CHECK(N % v == 0);
+        check_wide_grid<SNN_SPK_IO, v>(wide_grid<SNN_SPK_IO, v>(N, blk), blk, N);
+        return SNN_OK;
+    }
+};
+
+struct RelayProbe {
+    const Plan& p;
+    int64_t T, N;
+    template <typename K>
+    snn_status operator()(K) const {
+        CHECK(K::value == p.k && T > p.k);                        // at least two waves take turns
+        check_grid(grid_for(N, kWave), kWave, 1, N);
+        return SNN_OK;
+    }
+};
+
+template <int SPK>
+struct GainForwardProbe {
+    const Plan& p;
+    int64_t N;
+    template <typename V, typename FB, typename K, typename P, typename B>
+    snn_status operator()(V, FB, K, P, B) const {
+        CHECK(K::value == p.k && p.k % FB::value == 0 && N % V::value == 0);
+        check_wide_grid<SPK, V::value>(wide_grid<SPK, V::value>(N, B::value), B::value, N);
+        return SNN_OK;
+    }
+};
+
+struct GainBackwardProbe {
+    const Plan& p;
+    int64_t N;
+    template <typename V, typename K>
+    snn_status operator()(V, K) const {
+        CHECK(K::value == p.k && N % V::value == 0);
+        check_grid(grid_for((N + V::value - 1) / V::value), kBlock, V::value, N);
+        return SNN_OK;
+    }
+};
+
+template <int IO, int SPK>
+static void check_routes(const snn_lif_cfg& c, int64_t T, int64_t N) {
+    const Plan p = make_plan(&c, T, N), gp = make_gain_plan(&c, T, N);
+    const snn_status st[] = {forward_route<IO>(p, T, N, ForwardProbe<SPK>{p, T, N}),
+                             backward_route<IO>(p, T, N, BackwardProbe{p, T, N}, RelayProbe{p, T, N}),
+                             forward_gain_route<IO>(gp, GainForwardProbe<SPK>{gp, N}),
+                             backward_gain_route<IO>(gp, GainBackwardProbe{gp, N}, RelayProbe{gp, T, N})};
+    for (snn_status s : st) {
+        if (s != SNN_OK)
+            std::fprintf(stderr, "no kernel: route %d io %d spk %d T %lld N %lld vf %d vb %d k %d\n", int(&s - st), IO,
+                         SPK, (long long)T, (long long)N, p.vf, p.vb, p.k);
+        CHECK(s == SNN_OK);
+    }
+    const StackPlan sp = make_stack_plan(&c, T, N);
+    if (sp.v == 2) check_wide_grid<SPK, 2>(wide_grid<SPK, 2>(N), kBlock, N);
+    else check_wide_grid<SPK, 1>(wide_grid<SPK, 1>(N), kBlock, N);
+}
 
 static void check_plan(const snn_lif_cfg& c, int64_t T, int64_t N) {
     const Plan p = make_plan(&c, T, N);
     CHECK(p.vf == 1 || p.vf == 2 || p.vf == 4 || p.vf == 8);
     CHECK(p.vb == 1 || p.vb == 2 || p.vb == 4);
-    CHECK(N % p.vb == 0 && N % p.vf == 0);             // lanes never straddle the row end
+    CHECK(N % p.vb == 0 && N % p.vf == 0);
     CHECK(p.k == 4 || p.k == 8 || p.k == 16 || p.k == 32);
     CHECK(p.blkf == kBlock || p.blkf == kSyncBlock);
     CHECK(p.blkb == kBlock || p.blkb == kSyncBlock);
     if (p.blkf == kSyncBlock) CHECK(!p.pipe && T > p.k);
     if (p.blkb == kSyncBlock) CHECK(!p.pipe && T > p.k && p.vb == 2);
-    CHECK(p.lanes * p.vf >= N);
+    // one plan takes the place of vf, one that of vb, with the chunks it reads checkpoints by
+    CHECK(int(p.narrow) + int(p.widef) + int(p.rf > 0) <= 1);
+    CHECK(int(p.relay) + int(p.midsync) + int(p.rb > 0) <= 1);
+    if (p.widef) CHECK(p.k == 16 && N % 4 == 0 && c.io == SNN_IO_F32);
+    if (p.midsync) CHECK(p.k == 16 && p.vb == 2 && p.pipe);
+    if (p.rb == 4) CHECK(p.k <= 16);
+    if (p.narrow || p.relay) CHECK(T > p.k && N <= kNarrowN);
     CHECK(p.row_bytes == spike_row_bytes(&c, N));
-    if (c.spk == SNN_SPK_BITS) CHECK(p.lanes * p.vf >= p.row_bytes * 8);   // every spike word written
     const int64_t chunks = (T + p.k - 1) / p.k;
     CHECK(saved_bytes(p, T, N) == (chunks > 1 ? (chunks - 1) * N * 4 : 0));
     CHECK(saved_bytes(p, T, N) <= 4 * T * N);
-    snn_status fs, bs;
-    if (c.io == SNN_IO_F32) {
-        fs = forward_variant<SNN_IO_F32>(p, Probe{});
-        bs = backward_variant<SNN_IO_F32>(p, Probe{});
-    } else {
-        fs = forward_variant<SNN_IO_BF16>(p, Probe{});
-        bs = backward_variant<SNN_IO_BF16>(p, Probe{});
-    }
-    if (fs != SNN_OK || bs != SNN_OK)
-        std::fprintf(stderr, "no kernel variant: io %d T %lld N %lld vf %d vb %d k %d pipe %d\n", c.io,
-                     (long long)T, (long long)N, p.vf, p.vb, p.k, int(p.pipe));
-    CHECK(fs == SNN_OK && bs == SNN_OK);
     // the gain-fed layer: single-buffered chunks of the same length, so the same checkpoints
     const Plan gp = make_gain_plan(&c, T, N);
-    CHECK(!gp.pipe && gp.k == p.k && gp.vf == p.vf && gp.vb == p.vb && gp.lanes == p.lanes);
+    CHECK(!gp.pipe && gp.k == p.k && gp.vf == p.vf && gp.vb == p.vb);
     CHECK(saved_bytes(gp, T, N) == saved_bytes(p, T, N));
-    if (c.io == SNN_IO_F32) {
-        fs = forward_variant<SNN_IO_F32>(gp, Probe{});
-        bs = backward_variant<SNN_IO_F32>(gp, Probe{});
-    } else {
-        fs = forward_variant<SNN_IO_BF16>(gp, Probe{});
-        bs = backward_variant<SNN_IO_BF16>(gp, Probe{});
+    switch (c.io * 4 + c.spk) {
+        case SNN_IO_F32 * 4 + SNN_SPK_U8: check_routes<SNN_IO_F32, SNN_SPK_U8>(c, T, N); break;
+        case SNN_IO_F32 * 4 + SNN_SPK_BITS: check_routes<SNN_IO_F32, SNN_SPK_BITS>(c, T, N); break;
+        case SNN_IO_F32 * 4 + SNN_SPK_IO: check_routes<SNN_IO_F32, SNN_SPK_IO>(c, T, N); break;
+        case SNN_IO_BF16 * 4 + SNN_SPK_U8: check_routes<SNN_IO_BF16, SNN_SPK_U8>(c, T, N); break;
+        case SNN_IO_BF16 * 4 + SNN_SPK_BITS: check_routes<SNN_IO_BF16, SNN_SPK_BITS>(c, T, N); break;
+        case SNN_IO_BF16 * 4 + SNN_SPK_IO: check_routes<SNN_IO_BF16, SNN_SPK_IO>(c, T, N); break;
     }
-    if (fs != SNN_OK || bs != SNN_OK)
-        std::fprintf(stderr, "no gain-fed kernel variant: io %d T %lld N %lld vf %d vb %d k %d\n", c.io,
-                     (long long)T, (long long)N, gp.vf, gp.vb, gp.k);
-    CHECK(fs == SNN_OK && bs == SNN_OK);
     const StackPlan s = make_stack_plan(&c, T, N);
     CHECK((s.v == 1 || s.v == 2) && N % s.v == 0);
     CHECK(s.k == 4 || s.k == 8 || s.k == 16);
-    CHECK(s.lanes * s.v >= N);
     for (int L = 2; L <= kMaxStackLayers; ++L) {
         const int64_t sc = (T + s.k - 1) / s.k;
         CHECK(stack_saved_bytes(s, L, T, N) == (sc > 1 ? (sc - 1) * L * N * 4 : 0));
     }
 }
 
-static void check_plans() {
-    const int64_t Ns[] = {1, 2, 3, 7, 63, 64, 65, 1000, 4096, 4097, 65536, 131072, 524288, 1000000,
-                          (1 << 20) + 4, 8388608, (int64_t(1) << 22) + 2, 16777216, (int64_t(1) << 24) + 8,
-                          (int64_t(1) << 24) + 1, int64_t(1) << 28, kMaxN - 1, kMaxN};
-    const int64_t Ts[] = {1, 2, 3, 4, 5, 8, 9, 15, 16, 17, 31, 32, 33, 40, 64, 65, 96, 128, 192, 256, 257, 1000};
+static uint64_t rng_state = 0x9E3779B97F4A7C15ull;
+
+static double uniform() {   // xorshift64*, for test inputs only
+    rng_state ^= rng_state >> 12;
+    rng_state ^= rng_state << 25;
+    rng_state ^= rng_state >> 27;
+    return double((rng_state * 0x2545F4914F6CDD1Dull) >> 11) / double(uint64_t(1) << 53);
+}
+
+static void check_all(int64_t T, int64_t N) {
+    if (check_shape(T, N) != SNN_OK) return;
     for (int io : {SNN_IO_F32, SNN_IO_BF16})
-        for (int spk : {SNN_SPK_U8, SNN_SPK_BITS, SNN_SPK_IO})
-            for (int reset : {SNN_RESET_HARD, SNN_RESET_SOFT})
-                for (int64_t N : Ns)
-                    for (int64_t T : Ts) {
-                        if (check_shape(T, N) != SNN_OK) continue;
-                        check_plan(cfg(0.5f, 1.0f, reset, io, spk), T, N);
-                    }
+        for (int spk : {SNN_SPK_U8, SNN_SPK_BITS, SNN_SPK_IO}) check_plan(cfg(0.5f, 1.0f, SNN_RESET_HARD, io, spk), T, N);
+}
+
+static void check_plans() {
+    const int64_t wave = int64_t(256) * 64;
+    std::vector<int64_t> Ns = {1, 2, 3, 7, 63, 64, 65, 1000, 4096, 4097, 131072, 524288, 1000000, 8388608,
+                               (int64_t(1) << 22) + 2, 16777216, (int64_t(1) << 24) + 8, (int64_t(1) << 24) + 1,
+                               int64_t(1) << 28, kMaxN - 1, kMaxN};
+    // around the lines of the plans: waves of neurons per CU, filled rounds of synced
+    // workgroups, lanes that fill the chip
+    for (int64_t line : {wave, 5 * wave / 2, 3 * wave, 7 * wave / 2, int64_t(66) * 1024, kNarrowN, int64_t(1) << 17,
+                         int64_t(891289), int64_t(419430), int64_t(1) << 20, int64_t(1) << 21, int64_t(1) << 22})
+        for (int64_t d : {-4, -3, -2, -1, 0, 1, 2, 3, 4, 8, 64}) Ns.push_back(line + d);
+    const int64_t Ts[] = {1, 2, 3, 4, 5, 8, 9, 15, 16, 17, 31, 32, 33, 40, 48, 49, 63, 64, 65, 96, 100, 101, 128, 129,
+                          192, 193, 250, 251, 256, 257, 1000};
+    for (int64_t N : Ns)
+        for (int64_t T : Ts) check_all(T, N);
+    for (int i = 0; i < 20000; ++i)
+        check_all(int64_t(std::exp(uniform() * std::log(1200.0))), int64_t(std::exp(uniform() * std::log(4e7))));
 }
 
 // Sizes at which a plan lost against the general one: the rules keep them on the latter.
@@ -265,15 +374,6 @@ static void check_relay_rule() {
 }
 
 // ---------------------------------------------------------------- the oracle
-
-static uint64_t rng_state = 0x9E3779B97F4A7C15ull;
-
-static double uniform() {   // xorshift64*, for test inputs only
-    rng_state ^= rng_state >> 12;
-    rng_state ^= rng_state << 25;
-    rng_state ^= rng_state >> 27;
-    return double((rng_state * 0x2545F4914F6CDD1Dull) >> 11) / double(uint64_t(1) << 53);
-}
 
 static void run_oracle(int64_t T, int64_t B, int64_t F, int soft, bool nonfinite) {
     const int64_t N = B * F, TN = T * N;
