@@ -172,6 +172,15 @@ inline bool wide_sync_forward(const snn_lif_cfg* c, int64_t T, int64_t N) {
            (N * 4) % (int64_t(16) << 20) != 0;
 }
 
+// Even bf16 layers of several chunks whose N is no multiple of 8 take 8 neurons per lane in
+// place of 2 in the forward where the synced workgroups fill 0.62 of their rounds, 0.9 with byte
+// spikes: bit spikes 1.05-1.35 times as fast, spikes in the I/O dtype 1.0-1.24, byte spikes
+// 0.98-1.17; less filled, byte spikes 0.79-1.0 ([204][2448302] 340 -> 428 us, [90][4288218] 268 ->
+// 306 us), bit spikes [136][2149282] 187 -> 204 us.
+inline bool ragged_forward_fills(const snn_lif_cfg* c, int64_t N) {
+    return 100 * sync_fill(N, 8) >= (c->spk == SNN_SPK_U8 ? 90 : 62) * 256;
+}
+
 // The bf16 backward of large ragged layers (below) runs in kSyncBlock workgroups from this
 // many steps, a chunk and a tail in 256-lane ones.
 constexpr int64_t kSyncBf16From = 64;
@@ -219,7 +228,10 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     if (c->io == SNN_IO_BF16) {
         const int wf = N / 8 >= kFillLanes ? 8 : 2, wb = T <= 16 && N / 4 >= kFillLanes ? 4 : 2;
         const bool few = N <= kNarrowN;
-        p.rf = N > (T <= 8 ? int64_t(1) << 17 : kNarrowN) && wf > p.vf ? wf : 0;
+        p.rf = N > (T <= 8 ? int64_t(1) << 17 : kNarrowN) && wf > p.vf &&
+                       (wf < 8 || N % 2 != 0 || T <= p.k || ragged_forward_fills(c, N))
+                   ? wf
+                   : 0;
         p.rb = (!few || (T < p.k && N >= 4 * kWave)) && wb > p.vb ? wb : 0;
     }
     p.midsync = p.pipe && p.vb == 2 && sync_backward(c, T, N);
@@ -440,17 +452,14 @@ snn_status forward_route(const Plan& p, int64_t T, int64_t N, F&& f) {
     return forward_variant<IO>(p, [&](auto V, auto K, auto PIPE) -> snn_status {
         constexpr int Vc = decltype(V)::value, Kc = decltype(K)::value;
         constexpr bool Pc = decltype(PIPE)::value;
-        // bf16 layers of odd N and several chunks are narrow or ragged; 32-step chunks of even
-        // N take 8 neurons per lane
-        if constexpr (IO == SNN_IO_BF16 && ((Vc == 1 && Pc) || (Vc == 2 && Kc == 32))) {
-            return SNN_E_UNSUPPORTED;
-        } else {
-            constexpr IntC<forward_batch(IO, Vc, Kc, Pc)> FB{};
-            if constexpr (!Pc && Vc >= 2 && Kc == kLong) {
-                if (p.blkf == kSyncBlock) return f(V, FB, K, PIPE, IntC<kSyncBlock>{}, no);
-            }
-            return f(V, FB, K, PIPE, IntC<kBlock>{}, no);
+        constexpr IntC<forward_batch(IO, Vc, Kc, Pc)> FB{};
+        if constexpr (!Pc && Vc >= 2 && Kc == kLong) {
+            if (p.blkf == kSyncBlock) return f(V, FB, K, PIPE, IntC<kSyncBlock>{}, no);
         }
+        // bf16 layers of odd N and several chunks are narrow or ragged; a single 32-step chunk
+        // of even N takes 8 neurons per lane
+        if constexpr (IO == SNN_IO_BF16 && ((Vc == 1 && Pc) || (Vc == 2 && Kc == 32))) return SNN_E_UNSUPPORTED;
+        else return f(V, FB, K, PIPE, IntC<kBlock>{}, no);
     });
 }
 

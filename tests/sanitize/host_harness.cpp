@@ -317,6 +317,11 @@ static void check_ragged_rule() {
         for (int64_t T : {2, 15, 20}) CHECK(plan_of(SNN_IO_BF16, spk, T, 145).rb == 0);
         for (int64_t T : {3, 15, 20, 31}) CHECK(plan_of(SNN_IO_BF16, spk, T, 1201).rb == 2);
         for (int64_t T : {2, 5, 8}) CHECK(plan_of(SNN_IO_BF16, spk, T, 131071).rf == 0);
+        // 8 per lane over several chunks where they fill the chip
+        CHECK(plan_of(SNN_IO_BF16, spk, 146, 2208030).rf == 0);
+        CHECK(plan_of(SNN_IO_BF16, spk, 90, 4288218).rf == (spk == SNN_SPK_U8 ? 0 : 8));
+        CHECK(plan_of(SNN_IO_BF16, spk, 64, 4000002).rf == 8 && plan_of(SNN_IO_BF16, spk, 20, 2208030).rf == 8);
+        CHECK(plan_of(SNN_IO_BF16, spk, 146, 2208031).rf == 8);
         for (int64_t T : {9, 20, 33, 400}) {
             const Plan p = plan_of(SNN_IO_BF16, spk, T, 81921);
             CHECK(p.rf == 2 && p.rb == 2);
