@@ -539,10 +539,15 @@ __device__ __forceinline__ void forward_lanes(const LifK& c, const In& in, int64
 
 // Synced workgroups of kSyncBlock lanes run one to a CU: with two, which fewer registers
 // would allow, each CU walks two stretches of rows out of step (x[64][4194304] fp32 forward
-// 257 against 270 us, [100][3000000] 316 against 328 us).  7 waves per SIMD hold one such
-// workgroup of 16 waves, not two; the compiler reserves registers to that effect.
+// 257 against 270 us, [100][3000000] 316 against 328 us; bf16 spikes in the I/O dtype
+// [57][2380258] 144 against 154 us).  7 waves per SIMD hold one such workgroup of 16 waves,
+// not two; the compiler reserves registers to that effect.  fp32 layers of odd N and several
+// 32-step chunks, one neuron per lane, stay at 7 waves too (large ones 0.5-1.3% faster than
+// at 8, 150 sizes).
 constexpr int kMaxWaves = 8;   // per SIMD
-constexpr int waves_for(int blk) { return blk > kBlock ? 7 : kMaxWaves; }
+constexpr int waves_for(int io, int v, int k, bool pipe, int blk) {
+    return blk > kBlock || (io == SNN_IO_F32 && v == 1 && k == 32 && !pipe) ? 7 : kMaxWaves;
+}
 constexpr int min_waves_for(int blk) { return blk > kBlock ? 4 : 1; }
 
 // Grid (forward_grid): one lane per V neurons, the last workgroup's lanes guarded where they
@@ -556,7 +561,7 @@ constexpr int min_waves_for(int blk) { return blk > kBlock ? 4 : 1; }
 // (90 sizes; x[158][101010] 26.7 -> 27.5 us) and x[4][2^24] 0.7%; a uniform test in front of the
 // exit changed nothing.  Ragged forwards have one copy.
 template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock, bool RAGGED = false>
-__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(min_waves_for(BLK), waves_for(BLK))))
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(min_waves_for(BLK), waves_for(IO, V, KC, PIPE, BLK))))
 void lif_forward_kernel(LifK c, int64_t T, int64_t N,
                                                           const void* __restrict__ x,
                                                           uint8_t* __restrict__ spikes,
