@@ -172,13 +172,16 @@ inline bool wide_sync_forward(const snn_lif_cfg* c, int64_t T, int64_t N) {
            (N * 4) % (int64_t(16) << 20) != 0;
 }
 
-// Even bf16 layers of several chunks whose N is no multiple of 8 take 8 neurons per lane in
-// place of 2 in the forward where the synced workgroups fill 0.62 of their rounds, 0.9 with byte
-// spikes: bit spikes 1.05-1.35 times as fast, spikes in the I/O dtype 1.0-1.24, byte spikes
-// 0.98-1.17; less filled, byte spikes 0.79-1.0 ([204][2448302] 340 -> 428 us, [90][4288218] 268 ->
-// 306 us), bit spikes [136][2149282] 187 -> 204 us.
+// bf16 layers of several chunks whose N is no multiple of 8 take 8 neurons per lane in the
+// forward where the synced workgroups fill their rounds.  Even N, in place of 2 per lane, from
+// 0.62, with byte spikes 0.9: bit spikes 1.05-1.35 times as fast, spikes in the I/O dtype
+// 1.0-1.24, byte spikes 0.98-1.17; less filled, byte spikes 0.79-1.0 ([204][2448302] 340 -> 428
+// us, [90][4288218] 268 -> 306 us), bit spikes [136][2149282] 187 -> 204 us.  Odd N, in place of
+// one, always but for byte spikes under 0.62, where 8 per lane are 0.86-1.03 times as fast
+// ([50][2203833] 78.8 -> 91.7 us) and 2 per lane 1.03-1.27.
 inline bool ragged_forward_fills(const snn_lif_cfg* c, int64_t N) {
-    return 100 * sync_fill(N, 8) >= (c->spk == SNN_SPK_U8 ? 90 : 62) * 256;
+    const bool odd = N % 2 != 0, u8 = c->spk == SNN_SPK_U8;
+    return 100 * sync_fill(N, 8) >= (odd ? (u8 ? 62 : 0) : (u8 ? 90 : 62)) * 256;
 }
 
 // The bf16 backward of large ragged layers (below) runs in kSyncBlock workgroups from this
@@ -226,12 +229,10 @@ inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     // chunk gains there too ([20][1201] 12.1 -> 9.7 us).
     p.rf = p.rb = 0;
     if (c->io == SNN_IO_BF16) {
-        const int wf = N / 8 >= kFillLanes ? 8 : 2, wb = T <= 16 && N / 4 >= kFillLanes ? 4 : 2;
+        const int wf = N / 8 >= kFillLanes && (T <= p.k || ragged_forward_fills(c, N)) ? 8 : 2;
+        const int wb = T <= 16 && N / 4 >= kFillLanes ? 4 : 2;
         const bool few = N <= kNarrowN;
-        p.rf = N > (T <= 8 ? int64_t(1) << 17 : kNarrowN) && wf > p.vf &&
-                       (wf < 8 || N % 2 != 0 || T <= p.k || ragged_forward_fills(c, N))
-                   ? wf
-                   : 0;
+        p.rf = N > (T <= 8 ? int64_t(1) << 17 : kNarrowN) && wf > p.vf ? wf : 0;
         p.rb = (!few || (T < p.k && N >= 4 * kWave)) && wb > p.vb ? wb : 0;
     }
     p.midsync = p.pipe && p.vb == 2 && sync_backward(c, T, N);

@@ -321,7 +321,8 @@ static void check_ragged_rule() {
         CHECK(plan_of(SNN_IO_BF16, spk, 146, 2208030).rf == 0);
         CHECK(plan_of(SNN_IO_BF16, spk, 90, 4288218).rf == (spk == SNN_SPK_U8 ? 0 : 8));
         CHECK(plan_of(SNN_IO_BF16, spk, 64, 4000002).rf == 8 && plan_of(SNN_IO_BF16, spk, 20, 2208030).rf == 8);
-        CHECK(plan_of(SNN_IO_BF16, spk, 146, 2208031).rf == 8);
+        CHECK(plan_of(SNN_IO_BF16, spk, 50, 2203833).rf == (spk == SNN_SPK_U8 ? 2 : 8));
+        CHECK(plan_of(SNN_IO_BF16, spk, 173, 2884353).rf == 8);
         for (int64_t T : {9, 20, 33, 400}) {
             const Plan p = plan_of(SNN_IO_BF16, spk, T, 81921);
             CHECK(p.rf == 2 && p.rb == 2);
