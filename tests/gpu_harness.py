@@ -146,3 +146,45 @@ def round_io(a: np.ndarray, io: str) -> np.ndarray:
 __all__ = ["DEV", "say", "cfg_of", "to_dev", "to_host_f32", "upload_rows", "sample_columns", "gpu_layer",
            "compare_layer", "gather_columns", "check_full", "check_sampled", "synth_bf16", "round_io", "layer", "native", "np", "torch", "W",
            "oracle", "parity"]
+
+
+# Plans against each other on the same neurons: the same bit for bit.
+
+def as_bytes(t: torch.Tensor) -> torch.Tensor:
+    return t.contiguous().view(torch.uint8)
+
+
+def spike_columns(spikes: torch.Tensor, a: int, b: int, spk: str) -> torch.Tensor:
+    """Neurons [a, b) of spike rows as 0/1 bytes."""
+    if spk != "bits":
+        return (spikes[:, a:b] != 0).to(torch.uint8)
+    n = torch.arange(a, b, device=spikes.device)
+    return ((spikes[:, n >> 3] >> (n & 7).to(torch.uint8)) & 1).to(torch.uint8)
+
+
+def pack_spikes(y: torch.Tensor, spk: str, dtype: torch.dtype) -> torch.Tensor:
+    """0/1 rows [T, N] (bool) as the format stores them."""
+    if spk != "bits":
+        return y.to(dtype if spk == "io" else torch.uint8)
+    T, N = y.shape
+    row = 8 * ((N + 63) // 64)
+    bits = torch.zeros((T, row * 8), dtype=torch.uint8, device=y.device)
+    bits[:, :N] = y
+    return (bits.view(T, row, 8) << torch.arange(8, dtype=torch.uint8, device=y.device)).sum(2, dtype=torch.uint8)
+
+
+def sentinels(spikes: torch.Tensor, saved: torch.Tensor, v):
+    """Outputs of alloc_forward filled with what no kernel writes (spikes other than 0 and 1,
+    NaN membranes), so that a neuron left out shows."""
+    spikes.view(torch.uint8).fill_(0xA5)
+    saved.fill_(0xFF)
+    if v is not None:
+        v.fill_(float("nan"))
+    return spikes, saved, v
+
+
+def even_slices(N: int, width: int = 64000):
+    """Ranges of an even number of neurons, at most `width`, that cover all N (the last one
+    overlaps): layers this small take other plans than wide or ragged ones."""
+    w = min(width, N // 2 * 2)
+    return [(a, a + w) for a in range(0, N - w, w)] + [(N - w, N)]

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 NARROW_N = 5 * 256 * 64   # the largest layer that takes the narrow path
 
 SHAPES = [(17, 2), (33, 1), (40, 64), (47, 65), (128, 66), (129, 63), (150, 1000), (289, 127), (33, NARROW_N),
-          (40, NARROW_N - 1)]
+          (40, NARROW_N - 1), (129, 64001), (300, 69148)]   # the last two: backward not as a relay
 
 
 @pytest.fixture(scope="module")
@@ -22,19 +22,6 @@ def H():
         pytest.skip("no GPU")
     from tests import gpu_harness
     return gpu_harness
-
-
-def _bits(H, t):
-    return t.contiguous().view(H.torch.uint8)
-
-
-def _columns(H, spikes, a, b, spk):
-    """Neurons [a, b) of spike rows as 0/1 bytes."""
-    torch = H.torch
-    if spk != "bits":
-        return (spikes[:, a:b] != 0).to(torch.uint8)
-    n = torch.arange(a, b, device=spikes.device)
-    return ((spikes[:, n >> 3] >> (n & 7).to(torch.uint8)) & 1).to(torch.uint8)
 
 
 @pytest.mark.parametrize("T,N", SHAPES, ids=str)
@@ -58,26 +45,27 @@ def test_dense(H, T, N, reset, io, spk, segment):
             return spikes, saved, v, layer.backward(cfg, xs, saved, gss), ()
         v_in, g_in = state[0, lo:].clone(), state[1, lo:].clone()
         v_last, g_out = torch.empty_like(v_in), torch.empty_like(g_in)
-        out = layer.alloc_forward(cfg, T, n, H.DEV, True)
+        out = H.sentinels(*layer.alloc_forward(cfg, T, n, H.DEV, True))
         spikes, saved, v = layer.forward(cfg, xs, out=out, v_in=v_in, v_last=v_last)
         gx = layer.backward(cfg, xs, saved, gss, grad_x=gss, v_in=v_in, g_in=g_in, g_out=g_out)   # in place
         return spikes, saved, v, gx, (v_last, g_out)
 
     w, s = run(0), run(a)
-    assert torch.equal(_columns(H, s[0], 0, N, spk), _columns(H, w[0], a, wide, spk))
+    assert torch.equal(H.spike_columns(s[0], 0, N, spk), H.spike_columns(w[0], a, wide, spk))
     if spk == "bits" and N % 64:
-        pad = _columns(H, s[0], N, (N + 63) // 64 * 64, spk)
+        pad = H.spike_columns(s[0], N, (N + 63) // 64 * 64, spk)
         assert not pad.any()                          # padding bits are written as 0
     saved_w, saved_s = (t.view(torch.float32).view(-1, n) for t, n in ((w[1], wide), (s[1], N)))
-    assert torch.equal(_bits(H, saved_s), _bits(H, saved_w[:, a:]))
-    assert torch.equal(_bits(H, s[2]), _bits(H, w[2][:, a:]))
-    assert torch.equal(_bits(H, s[3]), _bits(H, w[3][:, a:]))
+    assert torch.equal(H.as_bytes(saved_s), H.as_bytes(saved_w[:, a:]))
+    assert torch.equal(H.as_bytes(s[2]), H.as_bytes(w[2][:, a:]))
+    assert torch.equal(H.as_bytes(s[3]), H.as_bytes(w[3][:, a:]))
     for narrow, whole in zip(s[4], w[4]):
-        assert torch.equal(_bits(H, narrow), _bits(H, whole[a:]))
+        assert torch.equal(H.as_bytes(narrow), H.as_bytes(whole[a:]))
 
 
-@pytest.mark.parametrize("T,B,F", [(17, 1, 2), (33, 3, 21), (40, 2, 33), (47, 7, 64), (150, 5, 200), (289, 16, 40)])
-@pytest.mark.parametrize("reset,io,spk", list(itertools.product(["hard", "soft"], ["f32", "bf16"], ["u8", "io"])))
+@pytest.mark.parametrize("T,B,F", [(17, 1, 2), (33, 3, 21), (40, 2, 33), (47, 7, 64), (150, 5, 200), (289, 16, 40),
+                                   (48, 1631, 33), (300, 692, 100)])
+@pytest.mark.parametrize("reset,io,spk", list(itertools.product(["hard", "soft"], ["f32", "bf16"], ["u8", "bits", "io"])))
 def test_gain(H, T, B, F, reset, io, spk):
     torch, layer = H.torch, H.layer
     cfg = layer.LifConfig(0.6, 0.9, v_reset=0.1, reset=reset, io=io, spk=spk)
@@ -85,15 +73,17 @@ def test_gain(H, T, B, F, reset, io, spk):
     Bw += (Bw - B) % 2                                # the same parity of N
     N, wide = B * F, Bw * F
     gen = torch.Generator(device=H.DEV).manual_seed(T * 7919 + N)
-    y = (torch.rand((T, wide), device=H.DEV, generator=gen) < 0.4).to(cfg.dtype if spk == "io" else torch.uint8)
+    y = torch.rand((T, wide), device=H.DEV, generator=gen) < 0.4
     gs = torch.empty((T, wide), dtype=cfg.dtype, device=H.DEV).normal_(generator=gen)
     gain = torch.empty(F, device=H.DEV).uniform_(-0.4, 1.6, generator=gen)
 
     def run(b):
         lo = (Bw - b) * F
-        ys, gss = y[:, lo:].contiguous(), gs[:, lo:].contiguous()
-        spikes, saved, v = layer.forward_gain(cfg, ys, gain, b, F, v_out=True)
-        return spikes, saved.view(torch.float32).view(-1, b * F), v, layer.backward_gain(cfg, ys, gain, saved, gss, b, F)
+        ys, gss = H.pack_spikes(y[:, lo:], spk, cfg.dtype), gs[:, lo:].contiguous()
+        out = H.sentinels(*layer.alloc_forward(cfg, T, b * F, H.DEV, True))
+        spikes, saved, v = layer.forward_gain(cfg, ys, gain, b, F, out=out)
+        gx = layer.backward_gain(cfg, ys, gain, saved, gss, b, F, grad_s_in=torch.full_like(gss, float("nan")))
+        return H.spike_columns(spikes, 0, b * F, spk), saved.view(torch.float32).view(-1, b * F), v, gx
 
     for narrow, whole in zip(run(B), run(Bw)):
-        assert torch.equal(_bits(H, narrow), _bits(H, whole[:, wide - N:]))
+        assert torch.equal(H.as_bytes(narrow), H.as_bytes(whole[:, wide - N:]))
