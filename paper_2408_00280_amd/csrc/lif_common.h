@@ -15,17 +15,18 @@ constexpr int64_t kMaxT = INT32_MAX;
 constexpr int64_t kMaxN = int64_t(1) << 31;
 constexpr int64_t kMaxTN = int64_t(1) << 44;
 
-// The neurons that lanes of V take: whole vectors, and whole words of bit-packed spikes (a
-// word of 64 neurons is shared by several lanes).  The few that are left go to one workgroup
-// of one neuron per lane, the first in the grid so that its long walk starts with the others;
-// no lane is guarded.
+// The neurons that lanes of V take in layers whose N need not be whole vectors (ragged bf16
+// layers) and in the gain-fed layers and stacks: whole vectors, and whole words of bit-packed
+// spikes (a word of 64 neurons is shared by several lanes).  The few that are left go to one
+// workgroup of one neuron per lane, the first in the grid so that its long walk starts with
+// the others; no lane is guarded.
 template <int SPK, int V>
 constexpr int64_t whole_vectors(int64_t N) {
     constexpr int64_t unit = SPK == SNN_SPK_BITS && V > 1 ? kWave : V;
     return N / unit * unit;
 }
 
-// Whether a layer whose N is a multiple of V can have such a rest.
+// Whether a gain-fed layer or a stack, whose N is a multiple of V, can have such a rest.
 template <int SPK, int V>
 constexpr bool has_rest() { return SPK == SNN_SPK_BITS && V > 1; }
 

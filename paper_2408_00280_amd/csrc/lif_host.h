@@ -184,10 +184,6 @@ inline bool ragged_forward_fills(const snn_lif_cfg* c, int64_t N) {
     return 100 * sync_fill(N, 8) >= (odd ? (u8 ? 62 : 0) : (u8 ? 90 : 62)) * 256;
 }
 
-// The bf16 backward of large ragged layers (below) runs in kSyncBlock workgroups from this
-// many steps, a chunk and a tail in 256-lane ones.
-constexpr int64_t kSyncBf16From = 64;
-
 inline Plan make_plan(const snn_lif_cfg* c, int64_t T, int64_t N) {
     Plan p;
     // 2 neurons per lane (fp32 8-byte rows: 4 per lane measured 1% slower on large layers;
@@ -478,7 +474,7 @@ snn_status backward_route(const Plan& p, int64_t T, int64_t N, F&& f, G&& relay)
             }
             return f(V, K, no, blk, no, yes);
         };
-        const bool sync_block = T > p.k && T >= kSyncBf16From && N / 2 >= 4 * kFillLanes;
+        const bool sync_block = T > p.k && N / 2 >= 4 * kFillLanes;
         if (p.rb == 4) return ragged_variant<4, false>(p, false, ragged);   // one chunk
         if (p.rb == 2) return ragged_variant<2, true>(p, sync_block, ragged);
     }

@@ -5,8 +5,11 @@
 // Design (see the header for the operation itself):
 //  * Neurons are independent (Sec. 3.1), so each lane owns V consecutive neurons and walks
 //    all T steps with their membranes in VGPRs (temporal fusion, Sec. 3.2).  Rows of the
-//    time-major [T][N] tensors are read and written coalesced along N, 8 or 16 bytes per
-//    lane (V = 2 fp32, V = 4 or 8 bf16 neurons) when N is a multiple of V; otherwise fewer.
+//    time-major [T][N] tensors are read and written coalesced along N, as a rule 2 neurons per
+//    lane (8-byte fp32, 4-byte bf16 rows); 4 or 8 on layers that fill the chip with them, 1 in
+//    fp32 layers of odd N and in layers of few neurons.  A vector needs only its elements'
+//    alignment: bf16 rows of odd N are read 2, 4 or 8 neurons per lane too, and the few neurons
+//    left over one per lane.
 //  * Time is processed in chunks of K steps.  All K input rows of a chunk are loaded before
 //    the first step of the chunk is computed (they do not depend on the recurrence), so
 //    every lane keeps K loads in flight.
