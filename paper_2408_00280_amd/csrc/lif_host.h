@@ -110,15 +110,16 @@ constexpr int64_t kWaveN = int64_t(256) * 64;   // neurons of one wave per CU
 // (x[44][77454] 0.83); fp32 spikes in the I/O dtype, many steps beyond three and a half waves
 // per CU 0.86-1.0 ([389][76402] 0.86, odd [706][62503] 0.88; odd N past 66 workgroups of 1,024
 // neurons 1.2-1.4).  Gain-fed layers, which it double-buffers and the other plan does not: bf16
-// spikes in the I/O dtype as the bit spikes ([47][74240] 0.70), and odd N of up to two 32-step
-// chunks ([48][53805] 0.76).
+// spikes in the I/O dtype as the bit spikes ([47][74240] 0.70), fp32 ones beyond four waves per
+// CU (0.87-1.1, [536][79050] 0.87), and odd N of up to three 32-step chunks ([48][53805] 0.76,
+// [93][62985] 0.72).
 inline bool narrow_forward(const snn_lif_cfg* c, int64_t T, int64_t N, int k, bool gain) {
     const bool f32 = c->io == SNN_IO_F32, odd = k == chunk_steps(1);
-    if (gain && odd && T <= 2 * k) return false;
+    if (gain && odd && T <= 3 * k) return false;
     if (!f32 && !odd && c->spk == (gain ? SNN_SPK_IO : SNN_SPK_BITS))
         return N <= kWaveN || T > (N <= 3 * kWaveN ? 64 : 128);
-    if (f32 && c->spk == SNN_SPK_IO && T > 8 * k && (odd || !gain))
-        return N <= 7 * kWaveN / 2 || (odd && N > 66 * 1024);
+    if (f32 && c->spk == SNN_SPK_IO && T > 8 * k)
+        return N <= (gain && !odd ? 4 * kWaveN : 7 * kWaveN / 2) || (odd && N > 66 * 1024);
     return true;
 }
 

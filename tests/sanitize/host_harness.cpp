@@ -343,9 +343,10 @@ static void check_narrow_forward_rule() {
         {SNN_IO_BF16, SNN_SPK_BITS, 64, 49152, false, true},  {SNN_IO_BF16, SNN_SPK_BITS, 65, 49152, true, true},
         {SNN_IO_BF16, SNN_SPK_BITS, 17, 16384, true, true},   {SNN_IO_BF16, SNN_SPK_IO, 47, 74240, true, false},
         {SNN_IO_BF16, SNN_SPK_IO, 26, 33820, true, false},    {SNN_IO_BF16, SNN_SPK_IO, 200, 74240, true, true},
-        {SNN_IO_F32, SNN_SPK_IO, 389, 76402, false, true},    {SNN_IO_F32, SNN_SPK_IO, 128, 76402, true, true},
+        {SNN_IO_F32, SNN_SPK_IO, 389, 76402, false, false},   {SNN_IO_F32, SNN_SPK_IO, 128, 76402, true, true},
+        {SNN_IO_F32, SNN_SPK_IO, 389, 65536, false, true},    {SNN_IO_BF16, SNN_SPK_IO, 93, 62985, true, false},
         {SNN_IO_F32, SNN_SPK_IO, 706, 62503, false, false},   {SNN_IO_F32, SNN_SPK_IO, 786, 81919, true, true},
-        {SNN_IO_F32, SNN_SPK_U8, 48, 53805, true, false},     {SNN_IO_F32, SNN_SPK_U8, 65, 53805, true, true},
+        {SNN_IO_F32, SNN_SPK_U8, 48, 53805, true, false},     {SNN_IO_F32, SNN_SPK_U8, 97, 53805, true, true},
         {SNN_IO_F32, SNN_SPK_U8, 1000, 8192, true, true},     {SNN_IO_BF16, SNN_SPK_U8, 1000, 81920, true, true}};
     for (const NarrowCase& r : cases) {
         const snn_lif_cfg c = cfg(0.5f, 1.0f, SNN_RESET_HARD, r.io, r.spk);

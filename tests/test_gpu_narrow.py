@@ -64,7 +64,7 @@ def test_dense(H, T, N, reset, io, spk, segment):
 
 
 @pytest.mark.parametrize("T,B,F", [(17, 1, 2), (33, 3, 21), (40, 2, 33), (47, 7, 64), (150, 5, 200), (289, 16, 40),
-                                   (48, 1631, 33), (300, 692, 100)])
+                                   (97, 3, 21), (161, 5, 33), (48, 1631, 33), (300, 692, 100)])
 @pytest.mark.parametrize("reset,io,spk", list(itertools.product(["hard", "soft"], ["f32", "bf16"], ["u8", "bits", "io"])))
 def test_gain(H, T, B, F, reset, io, spk):
     torch, layer = H.torch, H.layer
