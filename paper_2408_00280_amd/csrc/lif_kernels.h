@@ -562,7 +562,9 @@ constexpr int min_waves_for(int blk) { return blk > kBlock ? 4 : 1; }
 // A workgroup wholly inside N runs a copy of the code without any lane's exit: with one copy
 // under the per-lane exit the double-buffered bf16 backward of 55-110K neurons ran 2.5% slower
 // (90 sizes; x[158][101010] 26.7 -> 27.5 us) and x[4][2^24] 0.7%; a uniform test in front of the
-// exit changed nothing.  Ragged forwards have one copy.
+// exit changed nothing.  Ragged forwards have one copy, and fp32 ones of one neuron per lane and
+// bit spikes: two need more scalar registers than there are, and their tails ran 8% slower
+// (100 narrow layers; x[63][7517] 6.8 -> 9.8 us).
 template <int IO, int SPK, int RESET, int V, int K, int KC, bool VOUT, bool PIPE, int BLK = kBlock, bool RAGGED = false>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(min_waves_for(BLK), waves_for(IO, V, KC, PIPE, BLK))))
 void lif_forward_kernel(LifK c, int64_t T, int64_t N,
@@ -590,7 +592,8 @@ void lif_forward_kernel(LifK c, int64_t T, int64_t N,
     }
     const int64_t first = block * BLK * V, n0 = first + int64_t(threadIdx.x) * V;
     const DenseIn<IO, V> in{x};
-    if ((BLK > kBlock || !RAGGED) && first + BLK * V <= whole)
+    constexpr bool COPY = !RAGGED && !(IO == SNN_IO_F32 && SPK == SNN_SPK_BITS && V == 1);
+    if ((BLK > kBlock || COPY) && first + BLK * V <= whole)
         forward_lanes<IO, SPK, RESET, V, K, KC, VOUT, PIPE, DenseIn<IO, V>, (BLK > kBlock)>(
             c, in, T, N, n0, spikes, row_bytes, saved, v_out, v_in, v_last);
     else if (!RAGGED && SPK == SNN_SPK_BITS && V > 1)
